@@ -692,7 +692,7 @@ nk_status persistent_alloc(const LaunchPlan &plan, Params &p, Scratch &scr, hipS
     p.d = nullptr;
     p.lvl = nullptr;
     p.bmg = nullptr;
-    p.pair_rec = p.pair_blk = nullptr;
+    p.pair_rec = nullptr;
     p.lv2 = p.la2 = p.ld2 = nullptr;
     p.dist = nullptr;
     p.mark = nullptr;
@@ -708,32 +708,23 @@ nk_status persistent_alloc(const LaunchPlan &plan, Params &p, Scratch &scr, hipS
     if (pair) {
         // 32-byte records of both search sides, the target side's lists.
         // Every sample resets the records it touched, so a block left by a
-        // successful pair launch is still all-unreached and needs no fill;
-        // one record per vertex also holds the vertex's degree, refreshed
-        // on the device when the graph's row pointers differ from the ones
-        // the block was filled from (tables hold no degree).
+        // successful pair launch is still all-unreached and needs no fill,
+        // whatever graph the next launch runs on.
         const bool hashed = plan.mode == kModePairHash;
-        const long long head = hashed ? 0 : pair_block_head_bytes(plan.stride);
         bool clean = false;
         size_t blk_bytes = 0;
         void *blk = nullptr;
-        if ((st = scr.get_tagged((size_t)cells * 32 + (size_t)head, pair_block_tag(plan), &blk, &clean,
-                                 &blk_bytes)) != NK_OK)
+        if ((st = scr.get_tagged((size_t)cells * 32, pair_block_tag(plan), &blk, &clean, &blk_bytes)) != NK_OK)
             return st;
-        p.pair_blk = blk;
-        p.pair_rec = static_cast<char *>(blk) + head;
+        p.pair_rec = blk;
         if ((st = scr.get(cells, &p.lv2)) != NK_OK) return st;
         if ((st = scr.get(cells, &p.la2)) != NK_OK) return st;
         if ((st = scr.get(cells, &p.ld2)) != NK_OK) return st;
         if (hashed) {
             if ((st = scr.get(cells, &p.ls)) != NK_OK) return st;
             if ((st = scr.get(cells, &p.ls2)) != NK_OK) return st;
-            if (!clean) NK_HIP(launch_pair_table_init(blk, (long long)(blk_bytes / 32), s));
-        } else if (clean) {
-            NK_HIP(launch_pair_block_refresh(blk, blk_bytes, plan.stride, p.rowptr, p.n, s));
-        } else {
-            NK_HIP(launch_pair_block_init(blk, blk_bytes, plan.stride, p.rowptr, p.n, s));
         }
+        if (!clean) NK_HIP(launch_pair_rec_init(blk, (long long)(blk_bytes / 32), s));
     } else {
         if ((st = scr.get(cells, &p.sigma)) != NK_OK) return st;
         if ((st = scr.get(cells, &p.ldeg)) != NK_OK) return st;
@@ -1540,7 +1531,7 @@ static nk_status pair_run(const int32_t *rowptr, const int32_t *colidx, int32_t 
         p.defer_count = dcount;
     }
     if ((st = launch_persistent(plan, p, scr, s, ev0, hashed ? nullptr : ev1)) != NK_OK) return st;
-    plan.pair_rec = p.pair_blk;
+    plan.pair_rec = p.pair_rec;
     if (hashed) {
         unsigned long long nd = 0;
         NK_HIP(hipMemcpyAsync(&nd, dcount, sizeof(nd), hipMemcpyDeviceToHost, s));

@@ -33,11 +33,9 @@ nk_status dev_info(DevInfo *out);
 // Pooled device scratch.  Blocks return to the pool when the holder is
 // destroyed; the pool keeps them for later calls until nk_shutdown.
 // Scratch block tags (contents that stay meaningful across calls).
-// Pair-mode record blocks: every record unreached, and the degree field of
-// every record of every whole slot filled from the row pointers kept at the
-// block's head, for the record layout of the stride the tag carries.
+// Pair-mode record blocks: every record unreached (whatever graph or stride
+// the next launch brings).
 constexpr uint64_t kTagPairRecords = 1;
-inline uint64_t pair_records_tag(long long stride) { return kTagPairRecords | ((uint64_t)stride << 8); }
 // Pair-mode hash tables: every entry free and unreached.
 constexpr uint64_t kTagPairTables = 2;
 
@@ -114,9 +112,9 @@ struct LaunchPlan {
     long long dag_words;   // weighted mode: per-slot words of the DAG-arc bitmap
 };
 // The tag a pair-mode record block of `plan` carries after a successful
-// launch (records or hash tables, by the plan's mode and stride).
+// launch (records or hash tables, by the plan's mode).
 inline uint64_t pair_block_tag(const LaunchPlan &plan) {
-    return plan.mode == kModePairHash ? kTagPairTables : pair_records_tag(plan.stride);
+    return plan.mode == kModePairHash ? kTagPairTables : kTagPairRecords;
 }
 
 // Picks block size, bitmap placement and grid for graphs of at most n_max

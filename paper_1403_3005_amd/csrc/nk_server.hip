@@ -216,7 +216,7 @@ static void start_request(nk_server *sv, Slot &sl, Request *rq) {
             p.iso = g.iso;
             p.st = sl.dst;
             if ((st = launch_persistent(sl.plan, p, scr, s, nullptr, nullptr)) != NK_OK) return bail(st);
-            sl.plan.pair_rec = p.pair_blk;
+            sl.plan.pair_rec = p.pair_rec;
         }
         (void)launch_gather_u32(cnt, g.perm, n, cnt_orig, s);
         const double scale = r > 0 ? (double)n * (double)(n - 1) / (double)r : 0.0;
