@@ -405,8 +405,10 @@ nk_status nk_batch_plan_finish(nk_batch_plan *plan, void *stream);
  *   out[8] main kernel time in microseconds (HIP events on the call's stream)
  *   out[9] threads per workgroup
  *   out[10] kernel placement: 0 visited bitmap in global memory, 1 bitmap in
- *           LDS, 2 whole graph in LDS (all-in-LDS kernel), 3 a batch split
- *           between the all-in-LDS kernel and the LDS-bitmap kernel, 4 the
+ *           LDS (up to 65,534 vertices: the levels, and the path counts of
+ *           as many vertices as fit, in LDS instead), 2 whole graph in LDS
+ *           (all-in-LDS kernel), 3 a batch split between the all-in-LDS
+ *           kernel and those of 1, 4 the
  *           multi-source kernel, 5 a batch split between the all-in-LDS and
  *           multi-source kernels, 6 the group kernel (the workgroups of one
  *           XCD share a source), 7 a batch split between the all-in-LDS and
@@ -446,7 +448,10 @@ nk_status nk_last_stats(int64_t *out);
  *              of the internal degree-descending relabelling;
  *              bit 2: never use the all-in-LDS kernel (which otherwise runs
  *              betweenness on every graph whose CSR plus one source's state,
- *              about 16 n + 4 m bytes, fits one workgroup's LDS);
+ *              about 16 n + 2 m bytes, fits one workgroup's LDS), nor its
+ *              form with only the source's state in LDS (plain and linear
+ *              scaling, undirected graphs of up to 65,534 vertices, exact,
+ *              source-set and batched; also off under bits 0 and 3);
  *              bit 3: run exact and source-set betweenness (plain and linear
  *              scaling) of undirected graphs that the all-in-LDS kernel does
  *              not take on the group kernel, where the workgroups of one XCD

@@ -313,6 +313,11 @@ nk_status check_graph_args(const int32_t *rowptr, const int32_t *colidx, int32_t
 
 // ----------------------------------------------------------------- planner --
 
+// Largest graph of the state-in-LDS kernel: its 16-bit vertex ids.  (Exact
+// runs, ms, against the one-source kernel: 10^4 vertices 4.6 / 8.2, 1.6 *
+// 10^4 10.6 / 23, 2.5 * 10^4 34 / 55, 5 * 10^4 192 / 282, 6.5 * 10^4 320 / 454.)
+static const int32_t kStateMax = 65534;
+
 int auto_block(int32_t n_max) {
     if (n_max < 20000) return 256;
     if (n_max < 200000) return 512;
@@ -421,12 +426,15 @@ bool plan_lds(size_t dyn_bytes, int32_t n_max, long long ntasks, LaunchPlan *pla
         return false;
     }
     int block = t.block;
-    // levels of graphs above ~1500 vertices fill a 1024-thread tile; smaller
-    // ones leave room for two 512-thread workgroups per compute unit
-    if (block != 256 && block != 512 && block != 1024) block = n_max >= 1500 ? 1024 : 512;
-    KernelRef kr = brandes_lds_kernel(block);
+    KernelRef kr = brandes_lds_kernel(1024);
     hipFuncAttributes attr;
     if (hipFuncGetAttributes(&attr, kr.fn) != hipSuccess) return false;
+    // two 512-thread workgroups per compute unit where both fit (one works
+    // while the other is between levels: G(2000, 10000) 188 us against 225
+    // with one of 1024, G(1000, 4000) 74 against 95), else one of 1024
+    if (block != 256 && block != 512 && block != 1024)
+        block = 2 * (dyn_bytes + attr.sharedSizeBytes + 64) <= di.lds_per_block ? 512 : 1024;
+    kr = brandes_lds_kernel(block);
     if (attr.sharedSizeBytes + dyn_bytes > di.lds_per_block) return false;
     if (hipFuncSetAttribute(kr.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_bytes) != hipSuccess)
         return false;
@@ -446,6 +454,76 @@ bool plan_lds(size_t dyn_bytes, int32_t n_max, long long ntasks, LaunchPlan *pla
     plan->bm_words = 0;
     plan->kernel = kr;
     return true;
+}
+
+bool plan_state(int32_t n_max, long long ntasks, StatePlan *sp) {
+    const nk_tuning t = tuning_get();
+    if ((t.flags & (1 | 4 | 8)) || t.batch > 1 || n_max < 1 || n_max > kStateMax) return false;
+    DevInfo di;
+    if (dev_info(&di) != NK_OK) {
+        clear_error();
+        return false;
+    }
+    hipFuncAttributes attr;
+    if (hipFuncGetAttributes(&attr, brandes_state_kernel(1024, false).fn) != hipSuccess) return false;
+    const size_t room = di.lds_per_block > attr.sharedSizeBytes ? di.lds_per_block - attr.sharedSizeBytes : 0;
+    size_t dyn = lds_state_bytes(n_max);
+    const bool cold = dyn > room;
+    int32_t hot = n_max;
+    if (cold) {
+        const size_t fixed = lds_hot_bytes(n_max, 0);
+        if (fixed + 32 >= room) return false;
+        hot = (int32_t)((room - fixed - 32) / 8);
+        dyn = lds_hot_bytes(n_max, hot);
+    }
+    int block = t.block;
+    // as plan_lds: two 512-thread workgroups per compute unit where they fit
+    if (block != 256 && block != 512 && block != 1024)
+        block = !cold && 2 * (dyn + attr.sharedSizeBytes) <= di.lds_per_block ? 512 : 1024;
+    KernelRef kr = brandes_state_kernel(block, cold);
+    if (hipFuncSetAttribute(kr.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn) != hipSuccess) return false;
+    int occ = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kr.fn, block, dyn) != hipSuccess || occ < 1) return false;
+    if (t.wg_per_cu > 0 && t.wg_per_cu < occ) occ = t.wg_per_cu;
+    const long long stride = (((long long)n_max + 2) + 63) / 64 * 64;
+    long long grid = std::min<long long>((long long)di.cus * occ, ntasks);
+    if (cold && t.scratch_mib > 0) grid = std::min<long long>(grid, ((long long)t.scratch_mib << 20) / (stride * 12));
+    if (grid < 1) return false;
+    sp->cold = cold;
+    sp->hot = hot;
+    sp->lp.mode = kModeBC;
+    sp->lp.block = block;
+    sp->lp.lds = true;
+    sp->lp.grid = (int)grid;
+    sp->lp.dyn_lds = dyn;
+    sp->lp.stride = stride;
+    sp->lp.bm_words = 0;
+    sp->lp.kernel = kr;
+    sp->lp.pair_rec = nullptr;
+    sp->lp.dag_words = 0;
+    return true;
+}
+
+nk_status state_alloc(const StatePlan &sp, Params &p, Scratch &scr) {
+    nk_status st;
+    p.sigma = nullptr;
+    p.lv = nullptr;
+    if (sp.cold) {
+        if ((st = scr.get((long long)sp.lp.grid * sp.lp.stride, &p.sigma)) != NK_OK) return st;
+        if ((st = scr.get((long long)sp.lp.grid * sp.lp.stride, &p.lv)) != NK_OK) return st;
+    }
+    p.stride = sp.lp.stride;
+    p.lds_hot = sp.hot;
+    p.bu_ratio = tuning_get().bu_ratio;
+    return NK_OK;
+}
+
+nk_status state_enqueue(const StatePlan &sp, const Params &p, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+    if (ev0) NK_HIP(hipEventRecord(ev0, s));
+    sp.lp.kernel.launch(dim3(sp.lp.grid), dim3(sp.lp.block), sp.lp.dyn_lds, s, p);
+    NK_HIP(hipGetLastError());
+    if (ev1) NK_HIP(hipEventRecord(ev1, s));
+    return NK_OK;
 }
 
 // ------------------------------------------------------ multi-source plan --
@@ -957,7 +1035,12 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
         NK_HIP(launch_validate(dir->trp, dir->tci, n, m, 0, dst, s));
         if ((st = check_transpose(colidx, n, m, dir->trp, dst, scr, s)) != NK_OK) return st;
     }
-    NK_HIP(launch_fill_f64(bc, 0.0, n, s));
+    if (k == 0) NK_HIP(launch_fill_f64(bc, 0.0, n, s));
+    ScoreAcc sa;
+    if (k > 0) {
+        if ((st = score_acc(n, scr, &sa)) != NK_OK) return st;
+        NK_HIP(score_clear(sa, s));
+    }
     if (ebc) NK_HIP(launch_fill_f64(ebc, 0.0, m, s));
     LaunchPlan plan = {};
     float ms = 0.0f;
@@ -973,7 +1056,7 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
         p.m = (int32_t)m;
         p.ntasks = k;
         p.sources = sources;
-        p.bc = bc;
+        score_params(sa, &p);
         p.st = dst;
         p.linear = est == kEstLinear;
         hipEvent_t ev0, ev1;
@@ -982,14 +1065,20 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
         plan.kernel.launch(dim3(plan.grid), dim3(plan.block), plan.dyn_lds, s, p);
         NK_HIP(hipGetLastError());
         NK_HIP(hipEventRecord(ev1, s));
-        if (scale != 1.0) NK_HIP(launch_scale_f64(bc, scale, n, s));
+        NK_HIP(launch_gather_scores(sa, nullptr, scale, bc, s));
         st = finish(dst, h, s);
         NK_HIP(hipEventElapsedTime(&ms, ev0, ev1));
         where = 2;
     } else if (k > 0) {
         where = -1;
         Relabeled g = {rowptr, colidx, nullptr, nullptr};
-        if ((st = prepare_graph(rowptr, colidx, n, m, dst, scr, s, &g)) != NK_OK) return st;
+        // plain and linear-scaling sweeps of undirected graphs whose
+        // per-source state fits LDS; the renaming only pays where part of
+        // the path counts are outside it
+        StatePlan sp;
+        const bool state = !ebc && !dir && est != kEstBisect && plan_state(n, k, &sp);
+        if (!state || sp.cold)
+            if ((st = prepare_graph(rowptr, colidx, n, m, dst, scr, s, &g)) != NK_OK) return st;
         // a directed run renames its in-arcs with the same permutation
         DirectedArgs dir_run = {nullptr, nullptr};
         if (dir) {
@@ -1013,9 +1102,8 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
         // (directed; unknown without the in-arc CSR)
         if (dir)
             iso = dir->trp ? iso : nullptr;
-        if (iso) NK_HIP(launch_iso_bitmap(dir ? dir->trp : g.rowptr, n, iso, s));
+        if (iso && !state) NK_HIP(launch_iso_bitmap(dir ? dir->trp : g.rowptr, n, iso, s));
         const int32_t *src = sources;
-        double *acc = bc;
         if (g.perm) {
             if (sources) {
                 int32_t *mapped;
@@ -1023,8 +1111,28 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
                 NK_HIP(launch_map_sources(sources, (int32_t)k, g.perm, n, mapped, s));
                 src = mapped;
             }
-            if ((st = scr.get(n, &acc)) != NK_OK) return st;
-            NK_HIP(launch_fill_f64(acc, 0.0, n, s));
+        }
+        if (state) {
+            Params p;
+            memset(&p, 0, sizeof(p));
+            p.rowptr = g.rowptr;
+            p.colidx = g.colidx;
+            p.n = n;
+            p.m = (int32_t)m;
+            p.sources = src;
+            p.ntasks = k;
+            score_params(sa, &p);
+            p.st = dst;
+            p.linear = est == kEstLinear;
+            if ((st = state_alloc(sp, p, scr)) != NK_OK) return st;
+            hipEvent_t ev0, ev1;
+            if ((st = thread_events(&ev0, &ev1)) != NK_OK) return st;
+            if ((st = state_enqueue(sp, p, s, ev0, ev1)) != NK_OK) return st;
+            NK_HIP(launch_gather_scores(sa, g.perm, scale, bc, s));
+            st = finish(dst, h, s);
+            NK_HIP(hipEventElapsedTime(&ms, ev0, ev1));
+            stats_record(*h, sp.lp.grid, sp.lp.block, 1, ms);
+            return st;
         }
         // plain and linear-scaling sweeps of undirected graphs without edge
         // scores may run one source per XCD group of workgroups
@@ -1039,7 +1147,7 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
             p.m = (int32_t)m;
             p.sources = src;
             p.ntasks = k;
-            p.bc = acc;
+            score_params(sa, &p);
             p.iso = iso;
             p.st = dst;
             p.linear = est == kEstLinear;
@@ -1047,10 +1155,7 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
             hipEvent_t ev0, ev1;
             if ((st = thread_events(&ev0, &ev1)) != NK_OK) return st;
             if ((st = group_enqueue(gp, p, s, ev0, ev1)) != NK_OK) return st;
-            if (g.perm)
-                NK_HIP(launch_gather_scale(acc, g.perm, n, scale, bc, s));
-            else if (scale != 1.0)
-                NK_HIP(launch_scale_f64(bc, scale, n, s));
+            NK_HIP(launch_gather_scores(sa, g.perm, scale, bc, s));
             st = finish(dst, h, s);
             NK_HIP(hipEventElapsedTime(&ms, ev0, ev1));
             stats_record(*h, gp.lp.grid, gp.lp.block, 6, ms);
@@ -1070,7 +1175,7 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
             p.sources = src;
             p.nsources = k;
             p.ntasks = mp.ntasks;
-            p.bc = acc;
+            score_params(sa, &p);
             p.iso = iso;
             p.st = dst;
             p.linear = est == kEstLinear;
@@ -1078,10 +1183,7 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
             hipEvent_t ev0, ev1;
             if ((st = thread_events(&ev0, &ev1)) != NK_OK) return st;
             if ((st = ms_enqueue(mp, p, s, ev0, ev1)) != NK_OK) return st;
-            if (g.perm)
-                NK_HIP(launch_gather_scale(acc, g.perm, n, scale, bc, s));
-            else if (scale != 1.0)
-                NK_HIP(launch_scale_f64(bc, scale, n, s));
+            NK_HIP(launch_gather_scores(sa, g.perm, scale, bc, s));
             st = finish(dst, h, s);
             NK_HIP(hipEventElapsedTime(&ms, ev0, ev1));
             stats_record(*h, mp.lp.grid, mp.lp.block, 4, ms);
@@ -1097,7 +1199,7 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
         p.m = (int32_t)m;
         p.ntasks = k;
         p.sources = src;
-        p.bc = acc;
+        score_params(sa, &p);
         p.iso = iso;
         p.st = dst;
         p.linear = est == kEstLinear;
@@ -1108,10 +1210,7 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
         hipEvent_t ev0, ev1;
         if ((st = thread_events(&ev0, &ev1)) != NK_OK) return st;
         if ((st = launch_persistent(plan, p, scr, s, ev0, ev1)) != NK_OK) return st;
-        if (g.perm)
-            NK_HIP(launch_gather_scale(acc, g.perm, n, scale, bc, s));
-        else if (scale != 1.0)
-            NK_HIP(launch_scale_f64(bc, scale, n, s));
+        NK_HIP(launch_gather_scores(sa, g.perm, scale, bc, s));
         if (ebc && g.perm) NK_HIP(launch_arcs_back(ebc_run, g.rowptr, g.inv, rowptr, n, ebc, s));
         if (ebc) NK_HIP(launch_edge_symmetrize(rowptr, colidx, n, ebc, scale, dst, s));
         st = finish(dst, h, s);
@@ -1178,7 +1277,7 @@ nk_status nk_bc_weighted(const int32_t *rowptr, const int32_t *colidx, const int
     NK_HIP(launch_status_init(dst, s));
     NK_HIP(launch_validate(rowptr, colidx, n, m, 0, dst, s));
     if (m > 0) NK_HIP(launch_validate_weights(weights, m, dst, s));
-    NK_HIP(launch_fill_f64(bc, 0.0, n, s));
+    if (k == 0) NK_HIP(launch_fill_f64(bc, 0.0, n, s));
     LaunchPlan plan = {};
     float ms = 0.0f;
     if (k > 0) {
@@ -1203,7 +1302,9 @@ nk_status nk_bc_weighted(const int32_t *rowptr, const int32_t *colidx, const int
         Relabeled g = {rowptr, colidx, nullptr, nullptr};
         if ((st = prepare_graph(rowptr, colidx, n, m, dst, scr, s, &g)) != NK_OK) return st;
         const int32_t *wts = weights, *src = sources;
-        double *acc = bc;
+        ScoreAcc sa;
+        if ((st = score_acc(n, scr, &sa)) != NK_OK) return st;
+        NK_HIP(score_clear(sa, s));
         if (g.perm) {
             int32_t *w_new;
             if ((st = relabel_weights(weights, rowptr, n, m, g, dst, scr, s, &w_new)) != NK_OK) return st;
@@ -1214,8 +1315,6 @@ nk_status nk_bc_weighted(const int32_t *rowptr, const int32_t *colidx, const int
                 NK_HIP(launch_map_sources(sources, k, g.perm, n, mapped, s));
                 src = mapped;
             }
-            if ((st = scr.get(n, &acc)) != NK_OK) return st;
-            NK_HIP(launch_fill_f64(acc, 0.0, n, s));
         }
         if ((st = plan_launch(kModeWeighted, n, k, 0, &plan, m)) != NK_OK) return st;
         Params p;
@@ -1226,17 +1325,14 @@ nk_status nk_bc_weighted(const int32_t *rowptr, const int32_t *colidx, const int
         p.m = (int32_t)m;
         p.ntasks = k;
         p.sources = src;
-        p.bc = acc;
+        score_params(sa, &p);
         p.st = dst;
         p.wts = wts;
         p.wdelta = wdelta;
         hipEvent_t ev0, ev1;
         if ((st = thread_events(&ev0, &ev1)) != NK_OK) return st;
         if ((st = launch_persistent(plan, p, scr, s, ev0, ev1)) != NK_OK) return st;
-        if (g.perm)
-            NK_HIP(launch_gather_scale(acc, g.perm, n, scale, bc, s));
-        else if (scale != 1.0)
-            NK_HIP(launch_scale_f64(bc, scale, n, s));
+        NK_HIP(launch_gather_scores(sa, g.perm, scale, bc, s));
         st = finish(dst, h, s);
         NK_HIP(hipEventElapsedTime(&ms, ev0, ev1));
     } else {
@@ -1682,6 +1778,14 @@ struct BatchSetup {
     MsPlan mplan = {};
     GroupPlan gplan = {};      // the group kernel's launch
     Params pg;                 // its parameters (own scratch)
+    // state-in-LDS launches: [0] all path counts in LDS, [1] part of them
+    // global (own scratch)
+    struct StatePart {
+        StatePlan plan = {};
+        Params p;
+        long long *t = nullptr, k = 0;
+        int32_t *o = nullptr, g = 0, n = 0;
+    } state[2];
     long long *t_small = nullptr, *t_large = nullptr, *t_group = nullptr;
     int32_t *o_small = nullptr, *o_large = nullptr, *o_group = nullptr;
     long long k_small = 0, k_large = 0, k_group = 0;
@@ -1689,6 +1793,7 @@ struct BatchSetup {
     long long *d_vtx = nullptr, *d_arc = nullptr;
     int32_t G = 0;
     long long nv = 0;
+    ScoreAcc scores = {};
     const int32_t *rowptr = nullptr, *colidx = nullptr;
     double *bc = nullptr;
 };
@@ -1738,7 +1843,7 @@ static nk_status batch_prepare(int32_t G, const int64_t *vtx_off, const int64_t 
     }
     // Graphs the group kernel takes (by size, or all large ones under flag
     // bit 3) form a third part with a launch of its own.
-    std::vector<int32_t> small, large, grp;
+    std::vector<int32_t> small, large, grp, mid[2];
     int32_t n_small = 0;
     for (int32_t g = 0; g < G; ++g) {
         const long long ng = vtx_off[g + 1] - vtx_off[g], mg = arc_off[g + 1] - arc_off[g];
@@ -1782,10 +1887,10 @@ static nk_status batch_prepare(int32_t G, const int64_t *vtx_off, const int64_t 
     b->p.colidx = colidx_cat;
     b->p.g_vtx = b->d_vtx;
     b->p.g_arc = b->d_arc;
-    b->p.bc = bc_cat;
+    if ((st = score_acc(nv, scr, &b->scores)) != NK_OK) return st;
+    score_params(b->scores, &b->p);
     b->p.st = b->dst;
     b->g_small = (int32_t)small.size();
-    b->g_large = (int32_t)large.size();
     b->g_group = (int32_t)grp.size();
     if (!small.empty()) {
         if ((st = tables(small, &b->t_small, &b->o_small, &b->k_small, 1)) != NK_OK) return st;
@@ -1805,6 +1910,33 @@ static nk_status batch_prepare(int32_t G, const int64_t *vtx_off, const int64_t 
         use_cached = cached_tuning(nb, arc_off[gbig + 1] - arc_off[gbig], dmax, &cached);
     }
     TuningOverride cached_scope(use_cached ? &cached : nullptr);
+    {
+        // those whose per-source state fits LDS leave for its kernel
+        std::vector<int32_t> rest;
+        b->n_large = 0;
+        for (int32_t g : large) {
+            const int32_t ng = (int32_t)(vtx_off[g + 1] - vtx_off[g]);
+            StatePlan sp;
+            if (plan_state(ng, 1, &sp)) {
+                mid[sp.cold].push_back(g);
+                b->state[sp.cold].n = std::max(b->state[sp.cold].n, ng);
+            } else {
+                rest.push_back(g);
+                b->n_large = std::max(b->n_large, ng);
+            }
+        }
+        large.swap(rest);
+        b->g_large = (int32_t)large.size();
+        for (int q = 0; q < 2; ++q) {
+            BatchSetup::StatePart &sq = b->state[q];
+            if (mid[q].empty()) continue;
+            sq.g = (int32_t)mid[q].size();
+            if ((st = tables(mid[q], &sq.t, &sq.o, &sq.k, 1)) != NK_OK) return st;
+            if (!plan_state(sq.n, sq.k, &sq.plan)) return fail(NK_E_INTERNAL, "state-in-LDS plan failed");
+            sq.p = b->p;
+            if ((st = state_alloc(sq.plan, sq.p, scr)) != NK_OK) return st;
+        }
+    }
     if (!large.empty()) {
         long long nsrc_large = 0;
         for (int32_t g : large) nsrc_large += vtx_off[g + 1] - vtx_off[g];
@@ -1842,7 +1974,7 @@ static nk_status batch_prepare(int32_t G, const int64_t *vtx_off, const int64_t 
 static nk_status batch_enqueue(const BatchSetup &b, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     NK_HIP(launch_status_init(b.dst, s));
     NK_HIP(launch_validate_batched(b.rowptr, b.colidx, b.d_vtx, b.d_arc, b.G, b.dst, s));
-    NK_HIP(launch_fill_f64(b.bc, 0.0, b.nv, s));
+    NK_HIP(score_clear(b.scores, s));
     if (ev0) NK_HIP(hipEventRecord(ev0, s));
     Params p = b.p;
     if (b.g_small > 0) {
@@ -1854,8 +1986,23 @@ static nk_status batch_enqueue(const BatchSetup &b, hipStream_t s, hipEvent_t ev
         b.plan_s.kernel.launch(dim3(b.plan_s.grid), dim3(b.plan_s.block), b.plan_s.dyn_lds, s, p);
         NK_HIP(hipGetLastError());
     }
+    bool first = b.g_small == 0;
+    for (const BatchSetup::StatePart &sq : b.state) {
+        if (sq.g == 0) continue;
+        if (!first) NK_HIP(launch_reset_head(b.dst, s));
+        first = false;
+        Params q = sq.p;
+        q.n = sq.n;
+        q.G = sq.g;
+        q.g_task = sq.t;
+        q.g_order = sq.o;
+        q.ntasks = sq.k;
+        nk_status st = state_enqueue(sq.plan, q, s, nullptr, nullptr);
+        if (st != NK_OK) return st;
+    }
     if (b.g_large > 0) {
-        if (b.g_small > 0) NK_HIP(launch_reset_head(b.dst, s));
+        if (!first) NK_HIP(launch_reset_head(b.dst, s));
+        first = false;
         p.n = b.n_large;
         p.G = b.g_large;
         p.g_task = b.t_large;
@@ -1866,7 +2013,7 @@ static nk_status batch_enqueue(const BatchSetup &b, hipStream_t s, hipEvent_t ev
         if (st != NK_OK) return st;
     }
     if (b.g_group > 0) {
-        if (b.g_small > 0 || b.g_large > 0) NK_HIP(launch_reset_head(b.dst, s));
+        if (!first) NK_HIP(launch_reset_head(b.dst, s));
         Params q = b.pg;
         q.n = b.n_group;
         q.G = b.g_group;
@@ -1876,15 +2023,21 @@ static nk_status batch_enqueue(const BatchSetup &b, hipStream_t s, hipEvent_t ev
         nk_status st = group_enqueue(b.gplan, q, s, nullptr, nullptr);
         if (st != NK_OK) return st;
     }
+    NK_HIP(launch_gather_scores(b.scores, nullptr, 1.0, b.bc, s));
     if (ev1) NK_HIP(hipEventRecord(ev1, s));
     return NK_OK;
 }
 
 static void batch_stats(const BatchSetup &b, const DevStatus &h, float ms) {
+    const bool mid = b.state[0].g + b.state[1].g > 0;
     int where = b.g_large == 0 ? 2 : (b.g_small == 0 ? (b.plan_l.lds ? 1 : 0) : 3);
+    if (b.g_large == 0 && mid) where = b.g_small == 0 ? 1 : 3;
     if (b.g_large > 0 && b.ms_b > 1) where = b.g_small == 0 ? 4 : 5;
-    if (b.g_group > 0) where = (b.g_small == 0 && b.g_large == 0) ? 6 : 7;
-    const LaunchPlan &shown = b.g_large > 0 ? b.plan_l : (b.g_group > 0 ? b.gplan.lp : b.plan_s);
+    if (b.g_group > 0) where = (b.g_small == 0 && b.g_large == 0 && !mid) ? 6 : 7;
+    const LaunchPlan &shown = b.g_large > 0   ? b.plan_l
+                              : b.g_group > 0 ? b.gplan.lp
+                              : mid           ? b.state[b.state[1].g > 0 ? 1 : 0].plan.lp
+                                              : b.plan_s;
     stats_record(h, shown.grid, shown.block, where, ms);
     if (b.g_large > 0) stats_set_batch(b.ms_b);
 }

@@ -50,6 +50,11 @@ enum StatIdx {
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 __device__ __forceinline__ int wave_id() { return threadIdx.x / kWave; }
 
+// XCC (XCD) index of the executing compute unit.
+__device__ __forceinline__ int32_t xcc_id() {
+    return (int32_t)(__builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20) & 15u);
+}
+
 // SplitMix64 output function (Steele, Lea, Flood 2014).
 __device__ __forceinline__ uint64_t mix64(uint64_t z) {
     z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ULL;

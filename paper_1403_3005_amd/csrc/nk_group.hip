@@ -80,11 +80,6 @@ __device__ __forceinline__ unsigned long long u64_of(double x) { return (unsigne
 
 __device__ __forceinline__ bool lbit(const uint32_t *bm, int32_t v) { return (bm[v >> 5] >> (v & 31)) & 1u; }
 
-// XCC (XCD) index of the executing compute unit.
-__device__ __forceinline__ int32_t xcc_id() {
-    return (int32_t)(__builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20) & 15u);
-}
-
 // Workgroup-wide scalars (LDS).
 struct GState {
     int32_t group, rank, gsize, flag;
@@ -337,7 +332,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 1) void k_brandes_group(P
         }
         const int32_t nw = (n + 31) >> 5;
         const long long m_all = (long long)(rp[n] - rp[0]);
-        double *bcg = p.bc + vbase;
+        double *bcg = score_copy(p) + vbase;
 
         // this workgroup's bitmap: isolated vertices and padding marked
         for (int32_t wi = tid; wi < nw; wi += BLOCK) {

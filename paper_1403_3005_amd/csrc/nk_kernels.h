@@ -57,7 +57,10 @@ struct Params {
     int32_t pad2;
     int32_t maxlen;            // pair inspection
     // outputs
-    double *bc;
+    double *bc;                // scores: copy x (of bc_mask + 1) starts at bc + x * bc_x
+    long long bc_x;
+    int32_t bc_mask;
+    int32_t pad5;
     int32_t *d_out;
     unsigned long long *sigma_out;
     uint32_t *counts;
@@ -156,12 +159,20 @@ struct Params {
     // (defer, *defer_count)
     const long long *task_list;
     int32_t ph_log2;           // hashed records: log2 of the entries per slot (stride = 2^ph_log2)
-    int32_t pad3;
+    int32_t lds_hot;           // state-in-LDS kernel with cold path counts: vertices whose counts sit in LDS
     int32_t *ls;
     int32_t *ls2;
     long long *defer;
     unsigned long long *defer_count;
 };
+
+// The copy of the scores this workgroup adds into.  Every source adds to
+// every reached vertex, and an add from another XCD moves the line from
+// that XCD's L2 first; with a copy per XCD (summed at the end) the adds stay
+// in the XCD's own L2.
+__device__ __forceinline__ double *score_copy(const Params &p) {
+    return p.bc + (long long)(xcc_id() & p.bc_mask) * p.bc_x;
+}
 
 // Kernel handle for one (mode, block, bitmap placement) instantiation.
 struct KernelRef {
@@ -173,8 +184,16 @@ KernelRef brandes_kernel(int mode, int block, bool bitmap_in_lds);
 
 // All-in-LDS betweenness kernel for graphs whose CSR and per-source state
 // fit one workgroup's LDS (nk_lds.hip); lds_graph_bytes is its dynamic LDS
-// size for a graph of n vertices and m arcs.
+// size for a graph of n vertices and m arcs (too large to fit past 65,534
+// vertices).
 KernelRef brandes_lds_kernel(int block);
+// The same with only the per-source state in LDS (the graph in global
+// memory), lds_state_bytes of it; with cold = true the path counts of the
+// vertices from Params::lds_hot on, and the level lists, are in global
+// scratch and the LDS holds lds_hot_bytes.
+KernelRef brandes_state_kernel(int block, bool cold);
+size_t lds_state_bytes(int32_t n);
+size_t lds_hot_bytes(int32_t n, int32_t hot);
 
 // Multi-source kernel (nk_multi.hip) for `b` sources per task (4, 8 or
 // 16); its dynamic LDS holds the visited masks of the first vertices.

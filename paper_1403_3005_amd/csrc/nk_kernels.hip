@@ -2106,7 +2106,7 @@ __global__ __launch_bounds__(BLOCK, min_waves(BLOCK, MODE)) void k_brandes(Param
             phase_start<BLOCK>(sm);
             // the rows' ends of the sweep's tiles go where the staged
             // distances were
-            w_backward<BLOCK>(sm, s, g, Ld, p.bc, reinterpret_cast<int32_t *>(wsd), c);
+            w_backward<BLOCK>(sm, s, g, Ld, score_copy(p), reinterpret_cast<int32_t *>(wsd), c);
             phase_end<BLOCK>(sm, kPhPull);
             phase_start<BLOCK>(sm);
             for (int32_t i = tid; i < nreach; i += BLOCK) {
@@ -2155,7 +2155,7 @@ __global__ __launch_bounds__(BLOCK, min_waves(BLOCK, MODE)) void k_brandes(Param
                         atomicAdd(p.close_acc + s.lv[i], (unsigned long long)l);
             }
         } else if (MODE == kModeBC || MODE == kModeBisect) {
-            backward<BLOCK, MODE == kModeBisect>(p, sm, bm, s, g, Ld, p.bc + g.vbase, c);
+            backward<BLOCK, MODE == kModeBisect>(p, sm, bm, s, g, Ld, score_copy(p) + g.vbase, c);
         } else if (MODE == kModeSSSP) {
             const long long row = task * (long long)g.n;
             for (int32_t i = tid; i < nreached; i += BLOCK) {

@@ -705,7 +705,7 @@ __global__ __launch_bounds__(BLOCK) void k_brandes_ms(Params p) {
             }
             for (int32_t e = lo + tid; e < hi; e += BLOCK) vis_clear<B>(S, S.lv[e], S.lm[e]);
             __syncthreads();
-            double *bcg = p.bc + S.vbase;
+            double *bcg = score_copy(p) + S.vbase;
             for (int32_t l = Ld - 1; l >= 1; --l) {
                 const int32_t llo = S.lvl[l], lhi = S.lvl[l + 1];
                 const double wfac = p.linear ? (double)l / (double)(l + 1) : 1.0;

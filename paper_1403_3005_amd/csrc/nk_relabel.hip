@@ -59,10 +59,17 @@ __global__ void k_map_sources(const int32_t *src, int32_t k, const int32_t *perm
     }
 }
 
-__global__ void k_gather_scale(const double *in, const int32_t *perm, int32_t n, double scale, double *out) {
+// Scores of the caller's vertices: the sum of the copies, renamed (perm may
+// be NULL) and scaled.
+__global__ void k_gather_scores(const double *in, int32_t copies, long long x, const int32_t *perm, long long n,
+                                double scale, double *out) {
     const long long stride = (long long)gridDim.x * blockDim.x;
-    for (long long v = (long long)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride)
-        out[v] = in[perm[v]] * scale;
+    for (long long v = (long long)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
+        const long long i = perm ? perm[v] : v;
+        double s = in[i];
+        for (int c = 1; c < copies; ++c) s += in[c * x + i];
+        out[v] = s * scale;
+    }
 }
 
 __global__ void k_gather_u32(const uint32_t *in, const int32_t *perm, int32_t n, uint32_t *out) {
@@ -192,9 +199,24 @@ hipError_t launch_map_sources(const int32_t *src, int32_t k, const int32_t *perm
     return hipGetLastError();
 }
 
-hipError_t launch_gather_scale(const double *in, const int32_t *perm, int32_t n, double scale, double *out,
-                               hipStream_t s) {
-    hipLaunchKernelGGL(k_gather_scale, dim3(grid_of(n, 256)), dim3(256), 0, s, in, perm, n, scale, out);
+nk_status score_acc(long long n, Scratch &scr, ScoreAcc *a) {
+    a->copies = n <= kScoreCopiesMax ? kScoreCopies : 1;
+    a->x = (n + 31) / 32 * 32;   // whole lines
+    a->n = n;
+    return scr.get(a->copies * a->x, &a->acc);
+}
+
+void score_params(const ScoreAcc &a, Params *p) {
+    p->bc = a.acc;
+    p->bc_x = a.x;
+    p->bc_mask = a.copies - 1;
+}
+
+hipError_t score_clear(const ScoreAcc &a, hipStream_t s) { return launch_fill_f64(a.acc, 0.0, a.copies * a.x, s); }
+
+hipError_t launch_gather_scores(const ScoreAcc &a, const int32_t *perm, double scale, double *out, hipStream_t s) {
+    hipLaunchKernelGGL(k_gather_scores, dim3(grid_of(a.n, 256)), dim3(256), 0, s, a.acc, a.copies, a.x, perm, a.n, scale,
+                       out);
     return hipGetLastError();
 }
 

@@ -196,6 +196,21 @@ nk_status largest_unreached_component(const int32_t *rowptr, const int32_t *coli
 // tuning flag bit 2 turns the path off.
 bool plan_lds(size_t dyn_bytes, int32_t n_max, long long ntasks, LaunchPlan *plan);
 
+// State-in-LDS launch (nk_lds.hip): one source per workgroup, its path
+// counts and levels in LDS, the graph in global memory.
+struct StatePlan {
+    LaunchPlan lp;
+    bool cold;             // path counts from vertex `hot` on, and the lists, in global scratch
+    int32_t hot;
+};
+// Plans it for graphs of at most n_max vertices; false (nothing planned)
+// for larger ones than it takes and where the tuning asks for another
+// kernel (flag bits 0, 2 and 3, or a multi-source batch).
+bool plan_state(int32_t n_max, long long ntasks, StatePlan *sp);
+// Scratch of the launch, and the launch.
+nk_status state_alloc(const StatePlan &sp, Params &p, Scratch &scr);
+nk_status state_enqueue(const StatePlan &sp, const Params &p, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
+
 // Allocates per-slot scratch for `plan`, clears the path counts, fills the
 // scratch fields of `p` and launches the persistent kernel on `s`,
 // recording HIP events around it when ev0/ev1 are non-null.
@@ -246,8 +261,21 @@ hipError_t launch_map_sources(const int32_t *src, int32_t k, const int32_t *perm
                               hipStream_t s);
 hipError_t launch_arcs_back(const double *in, const int32_t *rp_new, const int32_t *inv, const int32_t *rowptr,
                             int32_t n, double *out, hipStream_t s);
-hipError_t launch_gather_scale(const double *in, const int32_t *perm, int32_t n, double scale, double *out,
-                               hipStream_t s);
+// Score accumulators of a run over n vertices (all graphs of a batch
+// together): one copy per XCD up to 2^25 vertices (8 x 8 bytes a vertex),
+// a single shared one above.
+constexpr int kScoreCopies = 8;
+constexpr long long kScoreCopiesMax = 1LL << 25;
+struct ScoreAcc {
+    double *acc;
+    long long n, x;        // vertices; doubles from one copy to the next
+    int copies;
+};
+nk_status score_acc(long long n, Scratch &scr, ScoreAcc *a);
+void score_params(const ScoreAcc &a, Params *p);
+hipError_t score_clear(const ScoreAcc &a, hipStream_t s);
+// out[v] = scale * sum of the copies at perm[v] (v where perm is NULL)
+hipError_t launch_gather_scores(const ScoreAcc &a, const int32_t *perm, double scale, double *out, hipStream_t s);
 hipError_t launch_gather_u32(const uint32_t *in, const int32_t *perm, int32_t n, uint32_t *out, hipStream_t s);
 
 // Vertex-diameter bound (see nk_vd_bound); runs synchronously on `s`.

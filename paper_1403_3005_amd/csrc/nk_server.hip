@@ -188,7 +188,8 @@ static void start_request(nk_server *sv, Slot &sl, Request *rq) {
         // scores in original ids, scaled by n / k, into a device buffer
         double *res;
         if ((st = scr.get(n, &res)) != NK_OK) return bail(st);
-        (void)launch_gather_scale(acc, g.perm, n, (double)n / (double)k, res, s);
+        // (one copy of the scores: the budget counts one)
+        (void)launch_gather_scores(ScoreAcc{acc, n, 0, 1}, g.perm, (double)n / (double)k, res, s);
         outd = res;
         (void)hipMemcpyAsync(sl.staging, outd, sizeof(double) * n, hipMemcpyDeviceToHost, s);
     } else {
