@@ -1429,6 +1429,23 @@ static nk_status closeness_impl(const int32_t *rowptr, const int32_t *colidx, in
     LaunchPlan plan = {};
     float ms = 0.0f;
     if (k > 0) {
+        // bit-parallel searches, unless memory or depth rule them out
+        hipEvent_t ev0, ev1;
+        if ((st = thread_events(&ev0, &ev1)) != NK_OK) return st;
+        NK_HIP(hipEventRecord(ev0, s));
+        bool done = false;
+        int levels = 0;
+        if ((st = close_bits(rowptr, colidx, n, m, sources, k, sampled, out, dst, scr, s, &done, &levels)) != NK_OK)
+            return st;
+        NK_HIP(hipEventRecord(ev1, s));
+        if (done) {
+            st = finish(dst, h, s);
+            NK_HIP(hipEventElapsedTime(&ms, ev0, ev1));
+            h->stat[kStSources] = (unsigned long long)k;
+            h->stat[kStBu] = (unsigned long long)levels;
+            stats_record(*h, (n + 63) / 64, 256, 0, ms);
+            return st;
+        }
         Relabeled g;
         if ((st = prepare_graph(rowptr, colidx, n, m, dst, scr, s, &g)) != NK_OK) return st;
         NK_HIP(launch_iso_bitmap(g.rowptr, n, iso, s));
@@ -1457,8 +1474,6 @@ static nk_status closeness_impl(const int32_t *rowptr, const int32_t *colidx, in
         p.st = dst;
         p.close_out = sampled ? nullptr : out;
         p.close_acc = acc;
-        hipEvent_t ev0, ev1;
-        if ((st = thread_events(&ev0, &ev1)) != NK_OK) return st;
         if ((st = launch_persistent(plan, p, scr, s, ev0, ev1)) != NK_OK) return st;
         if (sampled) NK_HIP(launch_close_finish(acc, g.perm, n, k, out, s));
         st = finish(dst, h, s);

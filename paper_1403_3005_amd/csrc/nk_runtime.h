@@ -191,6 +191,15 @@ nk_status grid_bfs(const int32_t *rowptr, const int32_t *colidx, int32_t n, int6
 nk_status largest_unreached_component(const int32_t *rowptr, const int32_t *colidx, int32_t n, const int32_t *skip,
                                       int32_t *label, int32_t *size, int32_t *flag, hipStream_t s, int32_t *out);
 
+// Closeness by bit-parallel searches, up to 1024 sources a pass
+// (nk_close.hip): exact (sources NULL, k = n) or sampled scores into out.
+// *done = false (nothing written but scratch and, for a source out of
+// range, the status) where the bits do not fit the scratch or the graph has
+// too many levels.  *levels: levels run.
+nk_status close_bits(const int32_t *rowptr, const int32_t *colidx, int32_t n, int64_t m, const int32_t *sources,
+                     int32_t k, bool sampled, double *out, DevStatus *dst, Scratch &scr, hipStream_t s, bool *done,
+                     int *levels);
+
 // All-in-LDS betweenness plan for graphs needing at most `dyn_bytes` of
 // dynamic LDS; returns false (and plans nothing) when they do not fit or
 // tuning flag bit 2 turns the path off.
