@@ -105,7 +105,9 @@ __device__ __forceinline__ int32_t wave_min(int32_t v) {
 // Shared-memory tile for BLOCK vertices plus block-level scalars.
 template <int BLOCK>
 struct Tile {
-    int32_t v[BLOCK];          // vertex ids
+    // tile_rows: each wave's row marks, four bytes a thread (zero between
+    // uses; tile_init clears them)
+    uint32_t mark[BLOCK];
     int32_t a0[BLOCK];         // rowptr[v]
     int32_t pre[BLOCK + 1];    // exclusive prefix of degrees, pre[cnt] = total arcs
     union {
@@ -192,6 +194,235 @@ __device__ __forceinline__ int32_t wave_append_pos(bool pred, int32_t value, int
     }
     atomicOr(err, kErrInternal);
     return -1;
+}
+
+template <int BLOCK>
+__device__ __forceinline__ void tile_init(Tile<BLOCK> &sm) {
+    sm.mark[threadIdx.x] = 0u;
+}
+
+// Inclusive prefix maximum over the wave (row shifts, then the row
+// broadcasts), values >= 0.
+__device__ __forceinline__ int32_t wave_prefix_max(int32_t x) {
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
+    return x;
+}
+
+// Tile rows and CSR positions of the thread's kTileArcs consecutive arcs of
+// the tile, base + kTileArcs * threadIdx.x ...: kk[j] = row, or -1 past the
+// tile's end.  Every thread of the wave calls it.
+//
+// A wave's 256 arcs are consecutive, so the wave finds the row of its first
+// arc once (two ballots over the prefix array), every later row that starts
+// among them leaves its number at its start position, and a prefix maximum
+// over the lanes hands each thread its row.  (A search per thread is ten
+// dependent LDS reads and a walk over the row starts, together half of the
+// arc loops' instructions.)  With the wave's rows, the heads' 16-byte loads
+// and add_to_rows: R-MAT scale 20, 4096 sources 460 ms to 417, scale 18,
+// 64 sources 8.4 ms to 7.1.
+constexpr int kTileArcs = 4;
+template <int BLOCK>
+__device__ __forceinline__ void tile_rows(Tile<BLOCK> &sm, int32_t cnt, int32_t total, int32_t base,
+                                          int32_t (&kk)[kTileArcs], int32_t (&arc)[kTileArcs]) {
+    constexpr int SPAN = kWave * kTileArcs, STEP = BLOCK / kWave;
+    const int lane = lane_id();
+    const int wid = __builtin_amdgcn_readfirstlane(wave_id());
+    const int32_t b0 = base + wid * SPAN;
+#pragma unroll
+    for (int j = 0; j < kTileArcs; ++j) {
+        kk[j] = -1;
+        arc[j] = 0;
+    }
+    if (b0 >= total) return;
+    // the last row that starts at or before b0
+    int32_t q = lane * STEP < cnt ? sm.pre[lane * STEP] : 0x7fffffff;
+    const int32_t blk = (int32_t)__popcll(__ballot(q <= b0)) - 1;
+    q = lane < STEP && blk * STEP + lane < cnt ? sm.pre[blk * STEP + lane] : 0x7fffffff;
+    const int32_t k0 = blk * STEP + (int32_t)__popcll(__ballot(q <= b0)) - 1;
+    const int32_t i = b0 + kTileArcs * lane;
+    // all of the wave's arcs in one long row: nothing to mark
+    if (sm.pre[k0 + 1] - b0 >= SPAN) {
+        const int32_t off = sm.a0[k0] - sm.pre[k0];
+#pragma unroll
+        for (int j = 0; j < kTileArcs; ++j) {
+            kk[j] = k0;
+            arc[j] = off + i + j;
+        }
+        return;
+    }
+    // (rows without arcs share their start with the row after them, and can
+    // put a row's number past a mark's 255)
+    asm volatile("" ::: "memory");
+    uint8_t *mark = reinterpret_cast<uint8_t *>(sm.mark) + wid * SPAN;
+    bool far = false;
+    for (int32_t k1 = k0 + 1; k1 < cnt; k1 += kWave) {
+        const int32_t k = k1 + lane;
+        const int32_t s = k < cnt ? sm.pre[k] - b0 : SPAN;
+        if (s < SPAN && sm.pre[k + 1] - b0 > s) {
+            mark[s] = (uint8_t)(k - k0);
+            far = far || k - k0 > 255;
+        }
+        if (__ballot(s < SPAN) != ~0ULL) break;
+    }
+    asm volatile("" ::: "memory");
+    const uint32_t f = sm.mark[threadIdx.x];
+    sm.mark[threadIdx.x] = 0u;
+    asm volatile("" ::: "memory");
+    if (__ballot(far)) {
+        if (i >= total) return;
+        int32_t k = k0, hi = cnt - 1;
+        while (k < hi) {
+            const int32_t mid = (k + hi + 1) >> 1;
+            if (sm.pre[mid] <= i)
+                k = mid;
+            else
+                hi = mid - 1;
+        }
+#pragma unroll
+        for (int j = 0; j < kTileArcs; ++j)
+            if (i + j < total) {
+                while (sm.pre[k + 1] <= i + j) ++k;
+                kk[j] = k;
+                arc[j] = sm.a0[k] - sm.pre[k] + i + j;
+            }
+        return;
+    }
+    int32_t m[kTileArcs];
+    m[0] = (int32_t)(f & 0xFFu);
+    m[1] = max(m[0], (int32_t)(f >> 8 & 0xFFu));
+    m[2] = max(m[1], (int32_t)(f >> 16 & 0xFFu));
+    m[3] = max(m[2], (int32_t)(f >> 24));
+    const int32_t before = __builtin_amdgcn_update_dpp(0, wave_prefix_max(m[3]), 0x138, 0xf, 0xf, false);
+    int32_t off = 0;
+#pragma unroll
+    for (int j = 0; j < kTileArcs; ++j) {
+        const int32_t k = k0 + max(before, m[j]);
+        if (i + j < total) {
+            if (j == 0 || k != kk[j > 0 ? j - 1 : 0]) off = sm.a0[k] - sm.pre[k];
+            kk[j] = k;
+            arc[j] = off + i + j;
+        }
+    }
+}
+
+// Heads of the thread's tile arcs (ci[0] or 0 where there is none).  Four
+// arcs of one row are one 16-byte load: the vector cache takes a line per
+// cycle, and four 4-byte loads each touch every line of the wave's kilobyte.
+// SHORT (mean degrees near 8, where few threads have one row): 16-byte loads
+// only where the whole wave can, and no branch per thread otherwise -- 200k
+// vertices of mean degree 8, 1024 sources: 26.1 ms against 26.8; R-MAT scale
+// 20 the other way round, 426 ms against 416.
+template <bool SHORT>
+__device__ __forceinline__ void tile_heads(const int32_t *ci, const int32_t (&kk)[kTileArcs],
+                                           const int32_t (&arc)[kTileArcs], int32_t (&w)[kTileArcs]) {
+    static_assert(kTileArcs == 4, "four arcs a thread");
+    struct __attribute__((packed, aligned(4))) Four { int32_t x[4]; };
+    const bool whole = kk[0] >= 0 && kk[0] == kk[3];
+    if (SHORT && __ballot(whole) != ~0ULL) {
+#pragma unroll
+        for (int j = 0; j < kTileArcs; ++j) w[j] = ci[(uint32_t)arc[j]];
+        return;
+    }
+#pragma unroll
+    for (int j = 0; j < kTileArcs; ++j) w[j] = 0;
+    if (whole) {
+        const Four f = *reinterpret_cast<const Four *>(ci + (uint32_t)arc[0]);
+#pragma unroll
+        for (int j = 0; j < kTileArcs; ++j) w[j] = f.x[j];
+    } else {
+#pragma unroll
+        for (int j = 0; j < kTileArcs; ++j)
+            if (kk[j] >= 0) w[j] = ci[(uint32_t)arc[j]];
+    }
+}
+
+template <int CTRL>
+__device__ __forceinline__ unsigned long long dpp_u64(unsigned long long x) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int32_t)(uint32_t)x, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int32_t)(uint32_t)(x >> 32), CTRL, 0xf, 0xf, true);
+    return ((unsigned long long)hi << 32) | lo;
+}
+// Addends of the tile's row sums: path counts (a wrap past 2^64 raises *ovf)
+// or FP64 terms.
+struct RowU64 {
+    using T = unsigned long long;
+    static __device__ __forceinline__ T add(T a, T b, bool &ovf) {
+        const T s = a + b;
+        ovf |= s < a;
+        return s;
+    }
+    template <int CTRL>
+    static __device__ __forceinline__ T step(T x, bool &ovf) { return add(x, dpp_u64<CTRL>(x), ovf); }
+    static __device__ __forceinline__ void to_row(T *p, T x, bool &ovf) {
+        const T o = atomicAdd(p, x);
+        ovf |= o + x < o;
+    }
+};
+struct RowF64 {
+    using T = double;
+    static __device__ __forceinline__ T add(T a, T b, bool &) { return a + b; }
+    template <int CTRL>
+    static __device__ __forceinline__ T step(T x, bool &) {
+        return x + __longlong_as_double((long long)dpp_u64<CTRL>((unsigned long long)__double_as_longlong(x)));
+    }
+    static __device__ __forceinline__ void to_row(T *p, T x, bool &) { atomicAdd(p, x); }
+};
+
+// Adds the thread's terms x[j] (zero: none) of its tile arcs, rows kk[j], to
+// the row sums in LDS.  Where sixteen threads in a row hold arcs of one row
+// only, their sum is formed first and added once: adds to one LDS address
+// are taken one after the other, and in a tile of hubs every thread of the
+// workgroup adds to the same few.  Every thread of the wave calls it.
+template <class R>
+__device__ __forceinline__ void add_to_rows(typename R::T *rows, const int32_t (&kk)[kTileArcs],
+                                            const typename R::T (&x)[kTileArcs], bool &ovf) {
+    using T = typename R::T;
+    static_assert(kTileArcs == 4, "four arcs a thread");
+    // the wave's arcs all in one row (in order, so the ends tell)
+    const int32_t first = __builtin_amdgcn_readlane(kk[0], 0), last = __builtin_amdgcn_readlane(kk[3], kWave - 1);
+    if (first == last) {
+        if (first < 0) return;
+        T s = R::add(R::add(x[0], x[1], ovf), R::add(x[2], x[3], ovf), ovf);
+        s = R::template step<0xB1>(s, ovf);
+        s = R::template step<0x4E>(s, ovf);
+        s = R::template step<0x141>(s, ovf);
+        s = R::template step<0x140>(s, ovf);
+        if ((lane_id() & 15) == 0 && s != (T)0) R::to_row(rows + first, s, ovf);
+        return;
+    }
+    int32_t k = kk[0];
+    T acc = x[0];
+#pragma unroll
+    for (int j = 1; j < kTileArcs; ++j) {
+        if (kk[j] >= 0 && kk[j] != k) {
+            if (acc != (T)0) R::to_row(rows + k, acc, ovf);
+            k = kk[j];
+            acc = (T)0;
+        }
+        if (kk[j] >= 0) acc = R::add(acc, x[j], ovf);
+    }
+    const int lane = lane_id();
+    // one row here, and the same as the lane before (in the 16)
+    const int32_t mine = kk[0] == k ? k : -2;
+    const int32_t prev = __builtin_amdgcn_update_dpp(0, mine, 0x111, 0xf, 0xf, false);
+    const bool same = mine >= 0 && ((lane & 15) == 0 || mine == prev);
+    const bool one = ((__ballot(same) >> (lane & 48)) & 0xFFFFULL) == 0xFFFFULL;
+    bool o16 = false;
+    T s = R::template step<0xB1>(acc, o16);    // lane ^ 1
+    s = R::template step<0x4E>(s, o16);        // lane ^ 2
+    s = R::template step<0x141>(s, o16);       // the other four of eight
+    s = R::template step<0x140>(s, o16);       // the other eight
+    if (one) {
+        ovf |= o16;
+        if ((lane & 15) == 0 && s != (T)0) R::to_row(rows + k, s, ovf);
+    } else if (acc != (T)0) {
+        R::to_row(rows + k, acc, ovf);
+    }
 }
 
 // Largest k in [0, cnt) with pre[k] <= i (pre[0] = 0 <= i).

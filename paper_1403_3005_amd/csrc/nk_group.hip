@@ -44,7 +44,7 @@ namespace nk {
 
 namespace {
 
-constexpr int kGChunk = 4;     // arcs per thread per pass of an arc loop
+constexpr int kGChunk = kTileArcs;   // arcs per thread per pass of an arc loop
 constexpr int kAccSlots = 4;   // rotating per-level accumulators
 
 struct alignas(128) GroupLine {
@@ -146,23 +146,37 @@ __device__ __forceinline__ int32_t gscan(int32_t x, int32_t *wsum, int32_t &tota
     return r;
 }
 
-// The thread's kGChunk arcs starting at tile arc i0: row kk[j] (or -1 past
-// the end) and head w[j].
+// The thread's kGChunk arcs of the tile from base + kGChunk * threadIdx.x on:
+// row kk[j] (or -1 past the end) and head w[j].
 template <int BLOCK>
-__device__ __forceinline__ void gchunk(const Tile<BLOCK> &sm, const int32_t *ci, int32_t cnt, int32_t total,
-                                       int32_t i0, int32_t (&kk)[kGChunk], int32_t (&w)[kGChunk]) {
-    int32_t k = (i0 < total) ? tile_search(sm.pre, cnt, i0) : 0;
+__device__ __forceinline__ void gchunk(Tile<BLOCK> &sm, const int32_t *ci, int32_t cnt, int32_t total, int32_t base,
+                                       int32_t (&kk)[kGChunk], int32_t (&w)[kGChunk]) {
+    int32_t arc[kGChunk];
+    tile_rows<BLOCK>(sm, cnt, total, base, kk, arc);
+    tile_heads<true>(ci, kk, arc, w);
+}
+
+// on[j] = bit w[j] of bm is set; the reads go out together.
+__device__ __forceinline__ void gbits(const uint32_t *bm, const int32_t (&w)[kGChunk], bool (&on)[kGChunk]) {
+    uint32_t x[kGChunk];
 #pragma unroll
-    for (int j = 0; j < kGChunk; ++j) {
-        const int32_t i = i0 + j;
-        kk[j] = -1;
-        w[j] = 0;
-        if (i < total) {
-            while (sm.pre[k + 1] <= i) ++k;
-            kk[j] = k;
-            w[j] = ci[sm.a0[k] + (i - sm.pre[k])];
-        }
-    }
+    for (int j = 0; j < kGChunk; ++j) x[j] = bm[(uint32_t)w[j] >> 5];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < kGChunk; ++j) on[j] = (x[j] >> (w[j] & 31)) & 1u;
+}
+
+// x[j] = sig[w[j]] for the active ones, 0 for the others (see gather in
+// nk_kernels.hip).
+__device__ __forceinline__ void ggather(const unsigned long long *sig, const int32_t (&w)[kGChunk],
+                                        const bool (&act)[kGChunk], unsigned long long (&x)[kGChunk]) {
+#pragma unroll
+    for (int j = 0; j < kGChunk; ++j) x[j] = 0ULL;
+#pragma unroll
+    for (int j = 0; j < kGChunk; ++j) x[j] = ldg_u64(sig + (act[j] ? (uint32_t)w[j] : 0u));
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < kGChunk; ++j) x[j] = act[j] ? x[j] : 0ULL;
 }
 
 // Appends the lanes' new vertices (fresh[j]: vertex v[j], first arc a0[j],
@@ -215,7 +229,6 @@ __device__ __forceinline__ int32_t gstage(Tile<BLOCK> &sm, const int32_t *lv, co
     int32_t dg = 0;
     if (tid < cnt) {
         const int32_t v = ldg_i32(lv + tb + tid);
-        sm.v[tid] = v;
         sm.a0[tid] = ldg_i32(la + tb + tid);
         dg = ldg_i32(ld + tb + tid);
         sm.val.u[tid] = ldg_u64(sig + v);
@@ -236,6 +249,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 1) void k_brandes_group(P
     __shared__ Tile<BLOCK> sm;
     __shared__ GState gs;
     const int tid = threadIdx.x;
+    tile_init<BLOCK>(sm);
     GroupCtl *ctls = reinterpret_cast<GroupCtl *>(p.xg_ctl);
     unsigned int *reg = p.xg_reg;   // [0, 16): workgroups per XCC id; [16]: total
 
@@ -414,7 +428,6 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 1) void k_brandes_group(P
                         v = cand[tb + tid];
                         a0 = rp[v];
                         dg = rp[v + 1] - a0;
-                        sm.v[tid] = v;
                         sm.a0[tid] = a0;
                         sm.val.u[tid] = 0ULL;
                     }
@@ -426,35 +439,18 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 1) void k_brandes_group(P
                     if (tid == 0) c.arcs_fwd += (unsigned long long)total;
                     for (int32_t rb = 0; rb < total; rb += BLOCK * kGChunk) {
                         int32_t kk[kGChunk], u[kGChunk];
-                        gchunk<BLOCK>(sm, ci, cnt, total, rb + tid * kGChunk, kk, u);
+                        gchunk<BLOCK>(sm, ci, cnt, total, rb, kk, u);
                         unsigned long long sv[kGChunk];
+                        bool act[kGChunk];
+                        gbits(lbm, u, act);
 #pragma unroll
-                        for (int j = 0; j < kGChunk; ++j)
-                            sv[j] = (kk[j] >= 0 && lbit(lbm, u[j])) ? ldg_u64(sig + u[j]) : 0ULL;
-                        int32_t kcur = kk[0];
-                        unsigned long long sacc = 0ULL;
+                        for (int j = 0; j < kGChunk; ++j) act[j] = (kk[j] >= 0) & act[j];
+                        ggather(sig, u, act, sv);
 #pragma unroll
-                        for (int j = 0; j < kGChunk; ++j) {
-                            if (kk[j] < 0) continue;
-                            if (kk[j] != kcur) {
-                                if (sacc) {
-                                    const unsigned long long o = atomicAdd(&sm.val.u[kcur], sacc);
-                                    if (o + sacc < o) atomicOr(&p.st->err, kErrOverflow);
-                                }
-                                kcur = kk[j];
-                                sacc = 0ULL;
-                            }
-                            if (sv[j]) {
-                                const unsigned long long ns = sacc + sv[j];
-                                if (ns < sacc) atomicOr(&p.st->err, kErrOverflow);
-                                sacc = ns;
-                                c.dag++;
-                            }
-                        }
-                        if (sacc) {
-                            const unsigned long long o = atomicAdd(&sm.val.u[kcur], sacc);
-                            if (o + sacc < o) atomicOr(&p.st->err, kErrOverflow);
-                        }
+                        for (int j = 0; j < kGChunk; ++j) c.dag += sv[j] ? 1u : 0u;
+                        bool ovf = false;
+                        add_to_rows<RowU64>(sm.val.u, kk, sv, ovf);
+                        if (ovf) atomicOr(&p.st->err, kErrOverflow);
                     }
                     __syncthreads();
                     bool fresh[1] = {false};
@@ -478,14 +474,15 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 1) void k_brandes_group(P
                     if (tid == 0) c.arcs_fwd += (unsigned long long)total;
                     for (int32_t rb = 0; rb < total; rb += BLOCK * kGChunk) {
                         int32_t kk[kGChunk], w[kGChunk];
-                        gchunk<BLOCK>(sm, ci, cnt, total, rb + tid * kGChunk, kk, w);
+                        gchunk<BLOCK>(sm, ci, cnt, total, rb, kk, w);
                         bool act[kGChunk], fresh[kGChunk];
                         unsigned long long add[kGChunk], old[kGChunk];
                         int32_t fa[kGChunk], fd[kGChunk];
+                        gbits(lbm, w, act);
 #pragma unroll
                         for (int j = 0; j < kGChunk; ++j) {
-                            act[j] = kk[j] >= 0 && !lbit(lbm, w[j]);
-                            add[j] = act[j] ? sm.val.u[kk[j]] : 0ULL;
+                            act[j] = (kk[j] >= 0) & !act[j];
+                            add[j] = sm.val.u[act[j] ? kk[j] : 0];
                         }
 #pragma unroll
                         for (int j = 0; j < kGChunk; ++j) old[j] = act[j] ? atomicAdd(sig + w[j], add[j]) : 1ULL;
@@ -570,28 +567,22 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 1) void k_brandes_group(P
                     if (tid == 0) c.arcs_bwd += (unsigned long long)total;
                     for (int32_t rb = 0; rb < total; rb += BLOCK * kGChunk) {
                         int32_t kk[kGChunk], w[kGChunk];
-                        gchunk<BLOCK>(sm, ci, cnt, total, rb + tid * kGChunk, kk, w);
+                        gchunk<BLOCK>(sm, ci, cnt, total, rb, kk, w);
+                        unsigned long long cb[kGChunk];
+                        bool act[kGChunk];
+                        gbits(lbm, w, act);
+#pragma unroll
+                        for (int j = 0; j < kGChunk; ++j) act[j] = (kk[j] >= 0) & !act[j];
+                        ggather(sig, w, act, cb);
                         double cf[kGChunk];
 #pragma unroll
-                        for (int j = 0; j < kGChunk; ++j)
-                            cf[j] = (kk[j] >= 0 && !lbit(lbm, w[j])) ? f64_of(ldg_u64(sig + w[j])) : 0.0;
-                        int32_t kcur = kk[0];
-                        double s = 0.0;
-#pragma unroll
-                        for (int j = 0; j < kGChunk; ++j) {
-                            if (kk[j] < 0) continue;
-                            if (kk[j] != kcur) {
-                                if (s != 0.0) atomicAdd(&sm.val.f[kcur], s);
-                                kcur = kk[j];
-                                s = 0.0;
-                            }
-                            s += cf[j];
-                        }
-                        if (s != 0.0) atomicAdd(&sm.val.f[kcur], s);
+                        for (int j = 0; j < kGChunk; ++j) cf[j] = f64_of(cb[j]);
+                        bool none = false;
+                        add_to_rows<RowF64>(sm.val.f, kk, cf, none);
                     }
                     __syncthreads();
                     if (tid < cnt) {
-                        const int32_t v = sm.v[tid];
+                        const int32_t v = ldg_i32(lv + tb + tid);
                         const double sg = (double)my_sigma;
                         const double delta = sg * sm.val.f[tid] * wfac;
                         sig[v] = u64_of((1.0 + delta) / sg);

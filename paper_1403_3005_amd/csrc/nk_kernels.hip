@@ -46,16 +46,16 @@
 //
 // Work inside a level is balanced over arcs, not vertices: a tile of up to
 // BLOCK listed vertices is staged in LDS with an exclusive prefix sum of
-// degrees, and each thread takes kChunk consecutive arcs of the tile (one
-// binary search, then a forward walk), so hubs with 10^5 arcs and leaves
-// share the same loop.  Each thread first issues the column loads of its
+// degrees, and each thread takes kChunk consecutive arcs of the tile (their
+// rows found by the wave together, tile_rows), so hubs with 10^5 arcs and
+// leaves share the same loop.  Each thread first issues the column loads of its
 // whole chunk, then the bitmap tests, then the path-count atomics or loads,
 // so several global accesses per lane are in flight at once.
 #include "nk_kernels.h"
 
 namespace nk {
 
-constexpr int kChunk = 4;
+constexpr int kChunk = kTileArcs;
 
 struct GView {
     const int32_t *rp;
@@ -131,7 +131,6 @@ __device__ __forceinline__ int32_t stage_list(Tile<BLOCK> &sm, const Scr &s, int
     const int tid = threadIdx.x;
     int32_t dg = 0;
     if (tid < cnt) {
-        sm.v[tid] = s.lv[tb + tid];
         sm.a0[tid] = s.la[tb + tid];
         dg = s.ld[tb + tid];
     }
@@ -151,7 +150,6 @@ __device__ __forceinline__ int32_t stage_ids(Tile<BLOCK> &sm, const int32_t *lis
     if (tid < cnt) {
         const int32_t v = list[tb + tid];
         const int32_t a0 = g.rp[v];
-        sm.v[tid] = v;
         sm.a0[tid] = a0;
         dg = g.rp[v + 1] - a0;
     }
@@ -162,23 +160,43 @@ __device__ __forceinline__ int32_t stage_ids(Tile<BLOCK> &sm, const int32_t *lis
     return total;
 }
 
-// Column indices of the thread's chunk [i0, i0 + kChunk) of the tile's arcs;
-// kk[j] = tile row of arc j, or -1 past the end.
+// Column indices of the thread's kChunk arcs of the tile from base +
+// kChunk * threadIdx.x on; kk[j] = tile row of arc j, or -1 past the end.
 template <int BLOCK>
-__device__ __forceinline__ void load_chunk(const Tile<BLOCK> &sm, const GView &g, int32_t cnt, int32_t total,
-                                           int32_t i0, int32_t (&kk)[kChunk], int32_t (&w)[kChunk]) {
-    int32_t k = (i0 < total) ? tile_search(sm.pre, cnt, i0) : 0;
+__device__ __forceinline__ void load_chunk(Tile<BLOCK> &sm, const GView &g, int32_t cnt, int32_t total, int32_t base,
+                                           int32_t (&kk)[kChunk], int32_t (&w)[kChunk]) {
+    int32_t arc[kChunk];
+    tile_rows<BLOCK>(sm, cnt, total, base, kk, arc);
+    tile_heads<false>(g.ci, kk, arc, w);
+}
+
+// x[j] = sigma[w[j]] (or 1, UNIT) for the active ones, 0 for the others.
+// The active bits are settled before the first load (test_bits) and every
+// lane loads, the inactive ones sigma[0]: with a branch around each load the
+// loads wait for one another, four round trips instead of one (R-MAT scale
+// 20, 4096 sources: 417 ms against 420 with the tests settled first and a
+// branch per load, 427 before both).
+template <bool UNIT>
+__device__ __forceinline__ void gather(const unsigned long long *sigma, const int32_t (&w)[kChunk],
+                                       const bool (&act)[kChunk], unsigned long long (&x)[kChunk]) {
 #pragma unroll
-    for (int j = 0; j < kChunk; ++j) {
-        const int32_t i = i0 + j;
-        kk[j] = -1;
-        w[j] = 0;
-        if (i < total) {
-            while (sm.pre[k + 1] <= i) ++k;
-            kk[j] = k;
-            w[j] = g.ci[sm.a0[k] + (i - sm.pre[k])];
-        }
-    }
+    for (int j = 0; j < kChunk; ++j) x[j] = UNIT && act[j] ? 1ULL : 0ULL;
+    if (UNIT) return;
+#pragma unroll
+    for (int j = 0; j < kChunk; ++j) x[j] = sigma[act[j] ? (uint32_t)w[j] : 0u];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < kChunk; ++j) x[j] = act[j] ? x[j] : 0ULL;
+}
+
+// on[j] = bit w[j] of bm is set; the reads go out together.
+__device__ __forceinline__ void test_bits(const uint32_t *bm, const int32_t (&w)[kChunk], bool (&on)[kChunk]) {
+    uint32_t x[kChunk];
+#pragma unroll
+    for (int j = 0; j < kChunk; ++j) x[j] = bm[(uint32_t)w[j] >> 5];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < kChunk; ++j) on[j] = (x[j] >> (w[j] & 31)) & 1u;
 }
 
 // Word-granular staging of the level list [tb, tb + cnt): row k's arc range
@@ -257,13 +275,14 @@ __device__ void td_level(const Params &p, Tile<BLOCK> &sm, uint32_t *bm, const S
         if (tid == 0) c.arcs_fwd += (unsigned long long)total;
         for (int32_t rb = 0; rb < total; rb += BLOCK * kChunk) {
             int32_t kk[kChunk], w[kChunk];
-            load_chunk<BLOCK>(sm, g, cnt, total, rb + tid * kChunk, kk, w);
+            load_chunk<BLOCK>(sm, g, cnt, total, rb, kk, w);
             bool act[kChunk];
             unsigned long long add[kChunk], old[kChunk];
+            test_bits(bm, w, act);
 #pragma unroll
             for (int j = 0; j < kChunk; ++j) {
-                act[j] = kk[j] >= 0 && !bit_test(bm, w[j]);
-                add[j] = act[j] ? sm.val.u[kk[j]] : 0ULL;
+                act[j] = (kk[j] >= 0) & !act[j];
+                add[j] = sm.val.u[act[j] ? kk[j] : 0];
             }
 #pragma unroll
             for (int j = 0; j < kChunk; ++j) old[j] = act[j] ? atomicAdd(&s.sigma[w[j]], add[j]) : 1ULL;
@@ -294,6 +313,8 @@ __device__ void bu_level(const Params &p, Tile<BLOCK> &sm, uint32_t *bm, const S
     g.ci = go.tci;
     const bool sym = go.trp == go.rp;
     const int32_t nw = (g.n + 31) >> 5;
+    bool ovf = false;
+    uint32_t dag = 0;
     if (tid == 0) sm.redmin = 0;  // candidate counter
     __syncthreads();
     for (int32_t wb = 0; wb < nw; wb += BLOCK) {
@@ -317,12 +338,11 @@ __device__ void bu_level(const Params &p, Tile<BLOCK> &sm, uint32_t *bm, const S
     sub_start<BLOCK>(sm);
     for (int32_t tb = 0; tb < nc; tb += BLOCK) {
         const int32_t cnt = min(BLOCK, nc - tb);
-        int32_t dg = 0;
+        int32_t dg = 0, w = 0;
         if (tid < cnt) {
-            const int32_t w = s.cand[tb + tid];
+            w = s.cand[tb + tid];
             const int32_t a0 = g.rp[w];
             dg = g.rp[w + 1] - a0;
-            sm.v[tid] = w;
             sm.a0[tid] = a0;
             sm.val.u[tid] = 0ULL;
         }
@@ -335,47 +355,24 @@ __device__ void bu_level(const Params &p, Tile<BLOCK> &sm, uint32_t *bm, const S
         if (tid == 0) c.arcs_fwd += (unsigned long long)total;
         for (int32_t rb = 0; rb < total; rb += BLOCK * kChunk) {
             int32_t kk[kChunk], v[kChunk];
-            load_chunk<BLOCK>(sm, g, cnt, total, rb + tid * kChunk, kk, v);
+            load_chunk<BLOCK>(sm, g, cnt, total, rb, kk, v);
             unsigned long long sv[kChunk];
+            bool act[kChunk];
+            test_bits(bm, v, act);
 #pragma unroll
-            for (int j = 0; j < kChunk; ++j) {
-                const bool act = kk[j] >= 0 && bit_test(bm, v[j]);
-                sv[j] = act ? ((MODE == kModeClose) ? 1ULL : s.sigma[v[j]]) : 0ULL;
-            }
-            int32_t kcur = kk[0];
-            unsigned long long acc = 0ULL;
+            for (int j = 0; j < kChunk; ++j) act[j] = (kk[j] >= 0) & act[j];
+            gather<MODE == kModeClose>(s.sigma, v, act, sv);
 #pragma unroll
-            for (int j = 0; j < kChunk; ++j) {
-                if (kk[j] < 0) continue;
-                if (kk[j] != kcur) {
-                    if (acc) {
-                        const unsigned long long o = atomicAdd(&sm.val.u[kcur], acc);
-                        if (o + acc < o) atomicOr(&p.st->err, kErrOverflow);
-                    }
-                    kcur = kk[j];
-                    acc = 0ULL;
-                }
-                if (sv[j]) {
-                    const unsigned long long nacc = acc + sv[j];
-                    if (nacc < acc) atomicOr(&p.st->err, kErrOverflow);
-                    acc = nacc;
-                    c.dag++;
-                }
-            }
-            if (acc) {
-                const unsigned long long o = atomicAdd(&sm.val.u[kcur], acc);
-                if (o + acc < o) atomicOr(&p.st->err, kErrOverflow);
-            }
+            for (int j = 0; j < kChunk; ++j) dag += sv[j] ? 1u : 0u;
+            add_to_rows<RowU64>(sm.val.u, kk, sv, ovf);
         }
         __syncthreads();
         sub_mark<BLOCK>(sm, kSbBuArcs);
         bool fresh = false;
-        int32_t w = 0;
         int32_t wa = 0, wd = 0;   // first out-arc and out-degree of the new vertex
         if (tid < cnt) {
             const unsigned long long sum = sm.val.u[tid];
             if (sum != 0ULL) {
-                w = sm.v[tid];
                 if (sym) {
                     wa = sm.a0[tid];
                     wd = dg;
@@ -409,6 +406,8 @@ __device__ void bu_level(const Params &p, Tile<BLOCK> &sm, uint32_t *bm, const S
         __syncthreads();
         sub_mark<BLOCK>(sm, kSbBuFin);
     }
+    c.dag += dag;
+    if (ovf) atomicOr(&p.st->err, kErrOverflow);
 }
 
 // Forward phase from `src`.  Returns the deepest non-empty level Ld; the
@@ -511,50 +510,45 @@ template <int BLOCK>
 __device__ void bw_pull(Tile<BLOCK> &sm, const uint32_t *bm, const Scr &s, const GView &g, int32_t lo, int32_t hi,
                         double *bcg, double wfac, double owt, double *ebc, bool add_bc, Counters &c) {
     const int tid = threadIdx.x;
+    bool none = false;
     sub_start<BLOCK>(sm);
     for (int32_t tb = lo; tb < hi; tb += BLOCK) {
         const int32_t cnt = min(BLOCK, hi - tb);
         if (tid < cnt) sm.val.f[tid] = 0.0;
+        const int32_t v = tid < cnt ? s.lv[tb + tid] : 0;
         const int32_t total = stage_list<BLOCK>(sm, s, tb, cnt);
         __syncthreads();
         sub_mark<BLOCK>(sm, kSbPlStage);
         if (tid == 0) c.arcs_bwd += (unsigned long long)total;
         for (int32_t rb = 0; rb < total; rb += BLOCK * kChunk) {
             int32_t kk[kChunk], w[kChunk];
-            load_chunk<BLOCK>(sm, g, cnt, total, rb + tid * kChunk, kk, w);
+            load_chunk<BLOCK>(sm, g, cnt, total, rb, kk, w);
+            unsigned long long cb[kChunk];
+            bool act[kChunk];
+            test_bits(bm, w, act);
+#pragma unroll
+            for (int j = 0; j < kChunk; ++j) act[j] = (kk[j] >= 0) & !act[j];
+            gather<false>(s.sigma, w, act, cb);
             double cf[kChunk];
 #pragma unroll
-            for (int j = 0; j < kChunk; ++j)
-                cf[j] = (kk[j] >= 0 && !bit_test(bm, w[j])) ? as_f64(s.sigma[w[j]]) : 0.0;
+            for (int j = 0; j < kChunk; ++j) cf[j] = as_f64(cb[j]);
             if (ebc) {
                 // edge term of the DAG arc v -> w: sigma_v * (1 + delta_w) / sigma_w
+                int32_t rv[kChunk];
+                unsigned long long sv[kChunk];
 #pragma unroll
-                for (int j = 0; j < kChunk; ++j) {
-                    if (cf[j] != 0.0) {
-                        const int32_t k = kk[j];
-                        const double sv = (double)s.sigma[sm.v[k]];
-                        atomicAdd(ebc + sm.a0[k] + (rb + tid * kChunk + j - sm.pre[k]), sv * cf[j]);
-                    }
-                }
-            }
-            int32_t kcur = kk[0];
-            double acc = 0.0;
+                for (int j = 0; j < kChunk; ++j) rv[j] = s.lv[tb + (act[j] ? kk[j] : 0)];
+                gather<false>(s.sigma, rv, act, sv);
 #pragma unroll
-            for (int j = 0; j < kChunk; ++j) {
-                if (kk[j] < 0) continue;
-                if (kk[j] != kcur) {
-                    if (acc != 0.0) atomicAdd(&sm.val.f[kcur], acc);
-                    kcur = kk[j];
-                    acc = 0.0;
-                }
-                acc += cf[j];
+                for (int j = 0; j < kChunk; ++j)
+                    if (act[j])
+                        atomicAdd(ebc + sm.a0[kk[j]] + (rb + tid * kChunk + j - sm.pre[kk[j]]), (double)sv[j] * cf[j]);
             }
-            if (acc != 0.0) atomicAdd(&sm.val.f[kcur], acc);
+            add_to_rows<RowF64>(sm.val.f, kk, cf, none);
         }
         __syncthreads();
         sub_mark<BLOCK>(sm, kSbPlArcs);
         if (tid < cnt) {
-            const int32_t v = sm.v[tid];
             const double sg = (double)s.sigma[v];
             const double delta = sg * sm.val.f[tid] * wfac;
             s.sigma[v] = as_u64((1.0 + delta) / sg);
@@ -588,16 +582,27 @@ __device__ void bw_push(Tile<BLOCK> &sm, const uint32_t *bm, const Scr &s, const
         if (tid == 0) c.arcs_bwd += (unsigned long long)total;
         for (int32_t rb = 0; rb < total; rb += BLOCK * kChunk) {
             int32_t kk[kChunk], v[kChunk];
-            load_chunk<BLOCK>(sm, g, cnt, total, rb + tid * kChunk, kk, v);
+            load_chunk<BLOCK>(sm, g, cnt, total, rb, kk, v);
+            bool act[kChunk];
+            test_bits(bm, v, act);
+#pragma unroll
+            for (int j = 0; j < kChunk; ++j) act[j] = (kk[j] >= 0) & act[j];
+            if (iso) {
+#pragma unroll
+                for (int j = 0; j < kChunk; ++j) act[j] = act[j] & !bit_test(iso, v[j]);
+            }
 #pragma unroll
             for (int j = 0; j < kChunk; ++j)
-                if (kk[j] >= 0 && bit_test(bm, v[j]) && !(iso && bit_test(iso, v[j]))) {
-                    const double cw = sm.val.f[kk[j]];
-                    atomicAdd(s.dacc + v[j], cw);
-                    if (ebc)
+                if (act[j]) atomicAdd(s.dacc + v[j], sm.val.f[kk[j]]);
+            if (ebc) {
+                unsigned long long sv[kChunk];
+                gather<false>(s.sigma, v, act, sv);
+#pragma unroll
+                for (int j = 0; j < kChunk; ++j)
+                    if (act[j])
                         atomicAdd(ebc + sm.a0[kk[j]] + (rb + tid * kChunk + j - sm.pre[kk[j]]),
-                                  (double)s.sigma[v[j]] * cw);
-                }
+                                  (double)sv[j] * sm.val.f[kk[j]]);
+            }
         }
         __syncthreads();
     }
@@ -668,7 +673,7 @@ __device__ void bis_group(Tile<BLOCK> &sm, uint32_t *bm, const Scr &s, const GVi
                 if (tid == 0) c.arcs_bwd += (unsigned long long)total;
                 for (int32_t rb = 0; rb < total; rb += BLOCK * kChunk) {
                     int32_t kk[kChunk], v[kChunk];
-                    load_chunk<BLOCK>(sm, g, cnt, total, rb + tid * kChunk, kk, v);
+                    load_chunk<BLOCK>(sm, g, cnt, total, rb, kk, v);
 #pragma unroll
                     for (int j = 0; j < kChunk; ++j)
                         if (kk[j] >= 0 && bit_test(bm, v[j]))
@@ -702,7 +707,7 @@ __device__ void bis_group(Tile<BLOCK> &sm, uint32_t *bm, const Scr &s, const GVi
                 if (tid == 0) c.arcs_bwd += (unsigned long long)total;
                 for (int32_t rb = 0; rb < total; rb += BLOCK * kChunk) {
                     int32_t kk[kChunk], w[kChunk];
-                    load_chunk<BLOCK>(sm, g, cnt, total, rb + tid * kChunk, kk, w);
+                    load_chunk<BLOCK>(sm, g, cnt, total, rb, kk, w);
                     int32_t kcur = kk[0];
                     double acc[kBisK] = {};
 #pragma unroll
@@ -734,7 +739,7 @@ __device__ void bis_group(Tile<BLOCK> &sm, uint32_t *bm, const Scr &s, const GVi
                 }
                 __syncthreads();
                 if (tid < cnt) {
-                    const int32_t v = sm.v[tid];
+                    const int32_t v = s.lv[tb + tid];
                     double *x = vec + (long long)v * kBisK;
                     const double sg = (double)s.sigma[v];
                     double add = 0.0;
@@ -843,8 +848,9 @@ constexpr unsigned long long kInf = ~0ULL;
 // order, so fewer of them are relaxed more than once.
 template <int BLOCK>
 __device__ int32_t w_distances(const Params &p, Tile<BLOCK> &sm, uint32_t *bm, const Scr &s, const GView &g,
-                               int32_t src, int32_t &ep, unsigned long long *sd, Counters &c) {
+                               int32_t src, int32_t &ep, Counters &c) {
     const int tid = threadIdx.x;
+    unsigned long long *sd = sm.val.u;   // distances of the staged vertices
     __shared__ int32_t s_reach, s_next, s_far, s_keep;
     const unsigned long long step = p.wdelta > 0 ? (unsigned long long)p.wdelta : kInf;
     unsigned long long thr = step;
@@ -883,43 +889,54 @@ __device__ int32_t w_distances(const Params &p, Tile<BLOCK> &sm, uint32_t *bm, c
         for (int32_t tb = 0; tb < ncur; tb += BLOCK) {
             const int32_t cnt = min(BLOCK, ncur - tb);
             const int32_t total = stage_ids<BLOCK>(sm, in, g, tb, cnt);
-            if (tid < cnt) sd[tid] = s.dist[sm.v[tid]];
+            if (tid < cnt) sd[tid] = s.dist[in[tb + tid]];
             __syncthreads();
             if (tid == 0) c.arcs_fwd += (unsigned long long)total;
             for (int32_t rb = 0; rb < total; rb += BLOCK * kChunk) {
-                int32_t kk[kChunk], w[kChunk];
-                load_chunk<BLOCK>(sm, g, cnt, total, rb + tid * kChunk, kk, w);
+                int32_t kk[kChunk], w[kChunk], arc[kChunk], wt[kChunk];
+                tile_rows<BLOCK>(sm, cnt, total, rb, kk, arc);
+                tile_heads<false>(g.ci, kk, arc, w);
+                tile_heads<false>(p.wts, kk, arc, wt);
+                // the four heads' distances in one round trip (an arc's
+                // weight, its head's distance, then the next arc's were eight;
+                // R-MAT scale 17, 256 sources: 28.0 ms to 26.3); a head that
+                // another arc improves meanwhile is settled by the atomic
+                // minimum below
+                bool on[kChunk];
+                unsigned long long nd[kChunk], cd[kChunk];
+                test_bits(bm, w, on);
+#pragma unroll
+                for (int j = 0; j < kChunk; ++j) on[j] = (kk[j] >= 0) & !on[j];
+                gather<false>(s.dist, w, on, cd);
                 int32_t word = -1;
                 uint32_t bits = 0u;
 #pragma unroll
                 for (int j = 0; j < kChunk; ++j) {
-                    bool first = false, queue = false, far = false;
-                    if (kk[j] >= 0 && !bit_test(bm, w[j])) {
-                        const int32_t k = kk[j];
-                        const int32_t arc = sm.a0[k] + (rb + tid * kChunk + j - sm.pre[k]);
-                        const unsigned long long nd = sd[k] + (unsigned long long)p.wts[arc];
-                        const unsigned long long cur = s.dist[w[j]];
-                        // an arc that ties or improves its head's distance may
-                        // end in the shortest-path DAG: every DAG arc does so
-                        // when its tail is relaxed at its final distance
-                        if (nd <= cur) {
-                            if ((arc >> 5) != word) {
-                                if (bits) atomicOr(&s.dagm[word], bits);
-                                word = arc >> 5;
-                                bits = 0u;
-                            }
-                            bits |= 1u << (arc & 31);
+                    nd[j] = sd[on[j] ? kk[j] : 0] + (unsigned long long)wt[j];
+                    // an arc that ties or improves its head's distance may
+                    // end in the shortest-path DAG: every DAG arc does so
+                    // when its tail is relaxed at its final distance
+                    if (on[j] && nd[j] <= cd[j]) {
+                        if ((arc[j] >> 5) != word) {
+                            if (bits) atomicOr(&s.dagm[word], bits);
+                            word = arc[j] >> 5;
+                            bits = 0u;
                         }
-                        if (nd < cur) {
-                            const unsigned long long old = atomicMin(&s.dist[w[j]], nd);
-                            if (nd < old) {
-                                first = old == kInf;
-                                if (nd < thr) {
-                                    queue = atomicExch(&s.mark[w[j]], ep) != ep;
-                                    s.d[w[j]] = 0;   // a far-pile entry of w is stale now
-                                } else {
-                                    far = atomicExch(&s.d[w[j]], 1) == 0;
-                                }
+                        bits |= 1u << (arc[j] & 31);
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < kChunk; ++j) {
+                    bool first = false, queue = false, far = false;
+                    if (on[j] && nd[j] < cd[j]) {
+                        const unsigned long long old = atomicMin(&s.dist[w[j]], nd[j]);
+                        if (nd[j] < old) {
+                            first = old == kInf;
+                            if (nd[j] < thr) {
+                                queue = atomicExch(&s.mark[w[j]], ep) != ep;
+                                s.d[w[j]] = 0;   // a far-pile entry of w is stale now
+                            } else {
+                                far = atomicExch(&s.d[w[j]], 1) == 0;
                             }
                         }
                     }
@@ -978,22 +995,23 @@ __device__ int32_t w_distances(const Params &p, Tile<BLOCK> &sm, uint32_t *bm, c
 // Returns the deepest layer.
 template <int BLOCK>
 __device__ int32_t w_layers_kahn(const Params &p, Tile<BLOCK> &sm, const Scr &s, const GView &g, int32_t src,
-                                 int32_t nreach, unsigned long long *sd, Counters &c) {
+                                 int32_t nreach, Counters &c) {
     const int tid = threadIdx.x;
+    unsigned long long *sd = sm.val.u;   // distances of the staged vertices, then their path counts
+    int32_t *ends = reinterpret_cast<int32_t *>(sm.mark);   // the rows' ends (the row marks are cleared after the sweep)
     for (int32_t i = tid; i < nreach; i += BLOCK) s.d[s.cand[i]] = 0;
     __syncthreads();
-    // DAG in-degrees, a thread per arc-bitmap word (candidate arcs only;
-    // the rows' ends take the place of the vertex ids)
+    // DAG in-degrees, a thread per arc-bitmap word (candidate arcs only)
     for (int32_t tb = 0; tb < nreach; tb += BLOCK) {
         const int32_t cnt = min(BLOCK, nreach - tb);
         if (tid < cnt) sd[tid] = s.dist[s.cand[tb + tid]];
-        const int32_t total = stage_words_ids<BLOCK>(sm, s.cand, g, tb, cnt, sm.v);
+        const int32_t total = stage_words_ids<BLOCK>(sm, s.cand, g, tb, cnt, ends);
         __syncthreads();
         for (int32_t wi = tid; wi < total; wi += BLOCK) {
             int32_t k;
             long long W;
             uint32_t bits;
-            tile_word<BLOCK>(sm, sm.v, cnt, wi, k, W, bits);
+            tile_word<BLOCK>(sm, ends, cnt, wi, k, W, bits);
             bits &= s.dagm[W];
             uint32_t drop = 0u;
             while (bits) {
@@ -1032,17 +1050,16 @@ __device__ int32_t w_layers_kahn(const Params &p, Tile<BLOCK> &sm, const Scr &s,
         for (int32_t tb = lo; tb < hi; tb += BLOCK) {
             const int32_t cnt = min(BLOCK, hi - tb);
             if (tid < cnt) sm.val.u[tid] = s.sigma[s.lv[tb + tid]];
-            // a thread per arc-bitmap word, DAG arcs only (the rows' ends
-            // take the place of the vertex ids); a head whose last DAG
-            // in-arc this is joins the next layer by an LDS counter
+            // a thread per arc-bitmap word, DAG arcs only; a head whose last
+            // DAG in-arc this is joins the next layer by an LDS counter
             int32_t deg;
-            const int32_t total = stage_words<BLOCK>(sm, s, tb, cnt, sm.v, deg);
+            const int32_t total = stage_words<BLOCK>(sm, s, tb, cnt, ends, deg);
             __syncthreads();
             for (int32_t wi = tid; wi < total; wi += BLOCK) {
                 int32_t k;
                 long long W;
                 uint32_t bits;
-                tile_word<BLOCK>(sm, sm.v, cnt, wi, k, W, bits);
+                tile_word<BLOCK>(sm, ends, cnt, wi, k, W, bits);
                 bits &= s.dagm[W];
                 while (bits) {
                     const int b = __builtin_ctz(bits);
@@ -1086,9 +1103,10 @@ __device__ int32_t w_layers_kahn(const Params &p, Tile<BLOCK> &sm, const Scr &s,
 // deepest layer.
 template <int BLOCK>
 __device__ int32_t w_layers_buckets(const Params &p, Tile<BLOCK> &sm, const Scr &s, const GView &g, int32_t src,
-                                    int32_t nreach, int32_t D, int32_t *hist, unsigned long long *sd,
+                                    int32_t nreach, int32_t D, int32_t *hist,
                                     Counters &c) {
     const int tid = threadIdx.x;
+    int32_t *ends = reinterpret_cast<int32_t *>(sm.mark);   // the rows' ends (the row marks are cleared after the sweep)
     for (int32_t b = tid; b < D; b += BLOCK) hist[b] = 0;
     __syncthreads();
     for (int32_t i = tid; i < nreach; i += BLOCK) atomicAdd(&hist[(int32_t)s.dist[s.cand[i]]], 1);
@@ -1127,19 +1145,17 @@ __device__ int32_t w_layers_buckets(const Params &p, Tile<BLOCK> &sm, const Scr 
             const int32_t cnt = min(BLOCK, hi - tb);
             if (tid < cnt) {
                 const int32_t v = s.lv[tb + tid];
-                sd[tid] = s.dist[v];
                 sm.val.u[tid] = s.sigma[v];
             }
-            // the rows' ends take the place of the vertex ids
             int32_t deg;
-            const int32_t total = stage_words<BLOCK>(sm, s, tb, cnt, sm.v, deg);
+            const int32_t total = stage_words<BLOCK>(sm, s, tb, cnt, ends, deg);
             __syncthreads();
             // a thread per bitmap word: only candidate arcs are looked at
             for (int32_t wi = tid; wi < total; wi += BLOCK) {
                 int32_t k;
                 long long W;
                 uint32_t bits;
-                tile_word<BLOCK>(sm, sm.v, cnt, wi, k, W, bits);
+                tile_word<BLOCK>(sm, ends, cnt, wi, k, W, bits);
                 bits &= s.dagm[W];
                 uint32_t drop = 0u;
                 while (bits) {
@@ -1147,7 +1163,7 @@ __device__ int32_t w_layers_buckets(const Params &p, Tile<BLOCK> &sm, const Scr 
                     bits &= bits - 1u;
                     const int32_t arc = (int32_t)(W * 32 + b);
                     const int32_t x = g.ci[arc];
-                    if (sd[k] + (unsigned long long)p.wts[arc] == s.dist[x]) {
+                    if ((unsigned long long)l + (unsigned long long)p.wts[arc] == s.dist[x]) {
                         const unsigned long long add = sm.val.u[k];
                         const unsigned long long o = atomicAdd(&s.sigma[x], add);
                         if (o + add < o) atomicOr(&p.st->err, kErrOverflow);
@@ -1169,7 +1185,7 @@ __device__ int32_t w_layers_buckets(const Params &p, Tile<BLOCK> &sm, const Scr 
 // Kahn layering.
 template <int BLOCK>
 __device__ int32_t w_layers(const Params &p, Tile<BLOCK> &sm, const Scr &s, const GView &g, int32_t src,
-                            int32_t nreach, int32_t *hist, unsigned long long *sd, Counters &c) {
+                            int32_t nreach, int32_t *hist, Counters &c) {
     __shared__ unsigned long long s_maxd;
     const int tid = threadIdx.x;
     if (tid == 0) s_maxd = 0ULL;
@@ -1189,8 +1205,8 @@ __device__ int32_t w_layers(const Params &p, Tile<BLOCK> &sm, const Scr &s, cons
     const unsigned long long maxd = s_maxd;
     __syncthreads();
     if (maxd + 1 <= (unsigned long long)kDistBuckets && (long long)maxd + 2 <= p.stride)
-        return w_layers_buckets<BLOCK>(p, sm, s, g, src, nreach, (int32_t)maxd + 1, hist, sd, c);
-    return w_layers_kahn<BLOCK>(p, sm, s, g, src, nreach, sd, c);
+        return w_layers_buckets<BLOCK>(p, sm, s, g, src, nreach, (int32_t)maxd + 1, hist, c);
+    return w_layers_kahn<BLOCK>(p, sm, s, g, src, nreach, c);
 }
 
 // Dependencies over the layers in reverse: delta_v = sigma_v * sum over DAG
@@ -1200,9 +1216,10 @@ __device__ int32_t w_layers(const Params &p, Tile<BLOCK> &sm, const Scr &s, cons
 // arcs on weighted graphs, whose shortest paths are mostly unique), so
 // the sweep reads no distances and no weights.
 template <int BLOCK>
-__device__ void w_backward(Tile<BLOCK> &sm, const Scr &s, const GView &g, int32_t Ld, double *bcg, int32_t *ends,
+__device__ void w_backward(Tile<BLOCK> &sm, const Scr &s, const GView &g, int32_t Ld, double *bcg,
                            Counters &c) {
     const int tid = threadIdx.x;
+    int32_t *ends = reinterpret_cast<int32_t *>(sm.mark);   // the rows' ends (the row marks are cleared after the sweep)
     if (Ld == 0) return;
     for (int32_t i = s.lvl[Ld] + tid; i < s.lvl[Ld + 1]; i += BLOCK) {
         const int32_t v = s.lv[i];
@@ -1215,7 +1232,6 @@ __device__ void w_backward(Tile<BLOCK> &sm, const Scr &s, const GView &g, int32_
             const int32_t cnt = min(BLOCK, hi - tb);
             if (tid < cnt) {
                 sm.val.f[tid] = 0.0;
-                sm.v[tid] = s.lv[tb + tid];
             }
             int32_t deg;
             const int32_t total = stage_words<BLOCK>(sm, s, tb, cnt, ends, deg);
@@ -1241,7 +1257,7 @@ __device__ void w_backward(Tile<BLOCK> &sm, const Scr &s, const GView &g, int32_
             }
             __syncthreads();
             if (tid < cnt) {
-                const int32_t v = sm.v[tid];
+                const int32_t v = s.lv[tb + tid];
                 const double sg = (double)s.sigma[v];
                 const double delta = sg * sm.val.f[tid];
                 s.sigma[v] = as_u64((1.0 + delta) / sg);
@@ -1437,7 +1453,7 @@ __device__ void pair_level(const Params &p, Tile<BLOCK> &sm, BiState &bs, const 
         if (tid == 0 && count_arcs) c.arcs_fwd += (unsigned long long)total;
         for (int32_t rb = 0; rb < total; rb += BLOCK * kChunk) {
             int32_t kk[kChunk], w[kChunk];
-            load_chunk<BLOCK>(sm, g, cnt, total, rb + tid * kChunk, kk, w);
+            load_chunk<BLOCK>(sm, g, cnt, total, rb, kk, w);
             bool act[kChunk];
             unsigned long long add[kChunk], old[kChunk];
             PairRec *e[kChunk];
@@ -1527,7 +1543,7 @@ __device__ void pair_probe(const Params &p, Tile<BLOCK> &sm, const Recs &R, int 
             int32_t kkq[U][kChunk], wq[U][kChunk];
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                load_chunk<BLOCK>(sm, g, cnt, total, rb + (u * BLOCK + tid) * kChunk, kkq[u], wq[u]);
+                load_chunk<BLOCK>(sm, g, cnt, total, rb + u * BLOCK * kChunk, kkq[u], wq[u]);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int32_t(&kk)[kChunk] = kkq[u];
@@ -1795,7 +1811,7 @@ __device__ void bidir_sample(const Params &p, Tile<BLOCK> &sm, BiState &bs, cons
             // one entry per thread when M fits the block: ids and weights in
             // the tile (its arrays are free once the search has ended)
             if (nm <= BLOCK) {
-                sm.v[tid] = oid;
+                sm.a0[tid] = oid;
                 sm.val.u[tid] = w;
             }
         }
@@ -1835,13 +1851,13 @@ __device__ void bidir_sample(const Params &p, Tile<BLOCK> &sm, BiState &bs, cons
                 // zero (counts that wrapped, already reported as overflow)
                 // can leave no such z; then z is the largest id, as the
                 // threshold search would end, so that z is always a vertex.
-                if (tid < nm && sm.v[tid] == thi_id) bs.z = sa.cand[tid];
+                if (tid < nm && sm.a0[tid] == thi_id) bs.z = sa.cand[tid];
                 __syncthreads();
                 if (tid < nm) {
-                    const int32_t me = sm.v[tid];
+                    const int32_t me = sm.a0[tid];
                     unsigned long long below = 0ULL;
                     for (int32_t k = 0; k < nm; ++k)
-                        if (sm.v[k] < me) below += sm.val.u[k];
+                        if (sm.a0[k] < me) below += sm.val.u[k];
                     if (below <= r0 && r0 - below < mine) bs.z = sa.cand[tid];
                 }
                 tlo_id = thi_id;   // the threshold search below has nothing to do
@@ -1947,6 +1963,7 @@ __global__ __launch_bounds__(BLOCK, min_waves(BLOCK, MODE)) void k_brandes(Param
     __shared__ Tile<BLOCK> sm;
     __shared__ BiState bs;
     const int tid = threadIdx.x;
+    tile_init<BLOCK>(sm);
     if (tid == 0) sm.flag = p.st->err & kErrGraph;
     __syncthreads();
     if (sm.flag) return;
@@ -1995,11 +2012,9 @@ __global__ __launch_bounds__(BLOCK, min_waves(BLOCK, MODE)) void k_brandes(Param
     __syncthreads();
     const long long t_kernel = clock64();
     int32_t ep = 0;                                   // weighted mode: round counter
-    __shared__ unsigned long long wsd[MODE == kModeWeighted ? BLOCK : 1];   // distances of staged vertices
     // pair modes: the two search sides' filters
     __shared__ uint32_t pfilt[MODE == kModePair || MODE == kModePairHash ? 2 * kPairFilterWords : 1];
     (void)ep;
-    (void)wsd;
     (void)pfilt;
     for (;;) {
         if (tid == 0) sm.task = (long long)atomicAdd(&p.st->head, 1ULL);
@@ -2095,18 +2110,17 @@ __global__ __launch_bounds__(BLOCK, min_waves(BLOCK, MODE)) void k_brandes(Param
             continue;
         } else if constexpr (MODE == kModeWeighted) {
             phase_start<BLOCK>(sm);
-            const int32_t nreach = w_distances<BLOCK>(p, sm, bm, s, g, src, ep, wsd, c);
+            const int32_t nreach = w_distances<BLOCK>(p, sm, bm, s, g, src, ep, c);
             phase_end<BLOCK>(sm, kPhTd);
             phase_start<BLOCK>(sm);
             // the distance-bucket histogram sits at the start of the dynamic
             // LDS (the settled bitmap's place when that is in LDS; it is not
             // needed past the distance rounds)
-            const int32_t Ld = w_layers<BLOCK>(p, sm, s, g, src, nreach, reinterpret_cast<int32_t *>(lds_bm), wsd, c);
+            const int32_t Ld = w_layers<BLOCK>(p, sm, s, g, src, nreach, reinterpret_cast<int32_t *>(lds_bm), c);
             phase_end<BLOCK>(sm, kPhBu);
             phase_start<BLOCK>(sm);
-            // the rows' ends of the sweep's tiles go where the staged
-            // distances were
-            w_backward<BLOCK>(sm, s, g, Ld, score_copy(p), reinterpret_cast<int32_t *>(wsd), c);
+            w_backward<BLOCK>(sm, s, g, Ld, score_copy(p), c);
+            tile_init<BLOCK>(sm);
             phase_end<BLOCK>(sm, kPhPull);
             phase_start<BLOCK>(sm);
             for (int32_t i = tid; i < nreach; i += BLOCK) {
