@@ -324,6 +324,26 @@ int auto_block(int32_t n_max) {
     return 1024;
 }
 
+// The same for one run over a graph of m arcs: wide levels feed a wide
+// workgroup, and with a compute unit a source the other waves would stay
+// empty.  Threads per workgroup 256 / 512 / 1024, ms (weighted, then edges
+// or directed): R-MAT scale 15, 16 sources 9.7 / 5.9 / 4.2 and 3.1 / 1.8 /
+// 1.2; scale 17, 256: 45 / 28 / 21 and 14 / 9.1 / 7.5; scale 17, 1024: 93 / 83 /
+// 68 and 29 / 26 / 23; 5 * 10^4 vertices of mean degree 8, 1024: 39 / 38 / 35
+// and 6.6 / 5.8 / 5.3; scale 13, 1024: 4.5 / 4.9 / 6.4 and 1.9 / 1.8 / 1.7.
+// Long thin graphs go the other way, since a level costs its barriers and
+// the sources run side by side (a 6 x 2500 grid, 1024 sources, 98 / 176 /
+// 326 and 27 / 47 / 83): below 6 arcs a vertex -- every planar graph, every
+// tree -- the vertices alone decide.
+static int auto_block_of(int mode, int32_t n, int64_t m, long long ntasks, int cus) {
+    const int block = auto_block(n);
+    if (block == 1024 || n < 1000 || m < 6LL * n) return block;
+    if (ntasks <= cus) return n >= 4000 ? 1024 : 512;
+    if (n < 2000) return block;   // 1,024 vertices, 300 sources' path counts: 0.20 ms, 0.23 with 512
+    if (n >= 20000) return m >= 12LL * n ? 1024 : block;
+    return mode != kModeWeighted || ntasks <= 2LL * cus ? 512 : block;
+}
+
 // Words of a per-slot bitmap over m arcs, rounded to 256 bytes.
 static long long dag_words_of(int64_t m) { return ((m + 31) / 32 + 63) / 64 * 64; }
 
@@ -334,7 +354,7 @@ nk_status plan_launch(int mode, int32_t n_max, long long ntasks, int max_slots, 
     nk_tuning t = tuning_get();
     int block = t.block;
     if (block != 256 && block != 512 && block != 1024) {
-        block = auto_block(n_max);
+        block = t.wg_per_cu > 0 ? auto_block(n_max) : auto_block_of(mode, n_max, m_arcs, ntasks, di.cus);
         // a pair sample's search levels are small: more concurrent samples
         // of 256 threads hide more memory latency than fewer wide ones
         if (mode == kModePair || mode == kModePairHash) block = 256;
@@ -1190,7 +1210,7 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
             stats_set_batch(msb);
             return st;
         }
-        if ((st = plan_launch(est == kEstBisect ? kModeBisect : kModeBC, n, k, 0, &plan)) != NK_OK) return st;
+        if ((st = plan_launch(est == kEstBisect ? kModeBisect : kModeBC, n, k, 0, &plan, m)) != NK_OK) return st;
         Params p;
         memset(&p, 0, sizeof(p));
         p.rowptr = g.rowptr;
@@ -1460,7 +1480,7 @@ static nk_status closeness_impl(const int32_t *rowptr, const int32_t *colidx, in
             if ((st = scr.get(n, &acc)) != NK_OK) return st;
             NK_HIP(launch_fill_u64(acc, 0ULL, n, s));
         }
-        if ((st = plan_launch(kModeClose, n, k, 0, &plan)) != NK_OK) return st;
+        if ((st = plan_launch(kModeClose, n, k, 0, &plan, m)) != NK_OK) return st;
         Params p;
         memset(&p, 0, sizeof(p));
         p.rowptr = g.rowptr;
@@ -1535,7 +1555,7 @@ nk_status nk_sssp_counts(const int32_t *rowptr, const int32_t *colidx, int32_t n
     NK_HIP(launch_fill_i32(d, -1, (long long)k * n, s));
     NK_HIP(launch_fill_u64((unsigned long long *)sigma, 0ULL, (long long)k * n, s));
     LaunchPlan plan;
-    if ((st = plan_launch(kModeSSSP, n, k, 0, &plan)) != NK_OK) return st;
+    if ((st = plan_launch(kModeSSSP, n, k, 0, &plan, m)) != NK_OK) return st;
     Params p;
     memset(&p, 0, sizeof(p));
     p.rowptr = g.rowptr;

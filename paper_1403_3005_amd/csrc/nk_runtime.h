@@ -119,7 +119,8 @@ inline uint64_t pair_block_tag(const LaunchPlan &plan) {
 
 // Picks block size, bitmap placement and grid for graphs of at most n_max
 // vertices and `ntasks` tasks.  max_slots > 0 caps the grid.  m_arcs: the
-// arcs of the graph (weighted mode sizes its DAG-arc bitmap by them).
+// arcs of the graph (weighted mode sizes its DAG-arc bitmap by them; 0 = not
+// known, and the block size then goes by the vertices alone).
 nk_status plan_launch(int mode, int32_t n_max, long long ntasks, int max_slots, LaunchPlan *plan,
                       int64_t m_arcs = 0);
 // Block size of a persistent launch over graphs of at most n_max vertices
