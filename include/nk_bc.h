@@ -459,7 +459,10 @@ nk_status nk_last_stats(int64_t *out);
  *              L2 (graphs whose visited bitmap fits LDS: up to about 1.1
  *              million vertices); block 512 makes two groups per XCD;
  *              bit 4: never use the group kernel (the automatic choice runs
- *              it on sparse graphs of 10^5 to 3 * 10^5 vertices);
+ *              it on sparse graphs of 10^5 to 3 * 10^5 vertices, and, with
+ *              block and wg_per_cu left at 0, for runs of at most half as
+ *              many sources as compute units on graphs of more than 65,534
+ *              vertices and at least 6 arcs a vertex);
  *              bit 5: pair sampling always keeps one record per vertex per
  *              workgroup slot; bit 6: it keeps a hash table of the reached
  *              vertices per slot instead (n/16 entries, rounded up to a
@@ -487,7 +490,7 @@ nk_status nk_last_stats(int64_t *out);
  *              chosen by graph size.
  *   group      workgroups per group in the group kernel (flags bit 3): 1,
  *              2, 4, 8, 16, 32 or 64, capped at the workgroups of one XCD
- *              (0 = chosen by graph size).  Each group runs one source at a
+ *              (0 = chosen by the number of sources).  Each group runs one source at a
  *              time; fewer workgroups per group means more sources in
  *              flight, more workgroups per group keeps fewer sources'
  *              path counts in the caches.

@@ -36,6 +36,7 @@ nk_status map_err(int32_t err) {
     if (err & kErrGraph) return fail(NK_E_INVALID_GRAPH, "CSR structure check failed");
     if (err & kErrArg) return fail(NK_E_INVALID_ARG, "a source or sample index is out of range");
     if (err & kErrOverflow) return fail(NK_E_SIGMA_OVERFLOW, "a shortest-path count needs 2^64 or more");
+    if (err & kErrBusy) return fail(NK_E_INTERNAL, "a group launch's workgroups were not resident in time");
     if (err & kErrInternal) return fail(NK_E_INTERNAL, "internal capacity check tripped");
     return NK_OK;
 }
@@ -656,7 +657,22 @@ nk_status ms_enqueue(const MsPlan &mp, const Params &p, hipStream_t s, hipEvent_
 
 // ------------------------------------------------------------- group plan --
 
-bool group_wanted(int32_t n_max, int64_t m_arcs) {
+// Groups and members a group on a device of `cus` compute units: the
+// tuning's S, else as many as there are compute units a source, 4 at least
+// (with sources for every group 4 measured fastest on mid-size graphs:
+// whole-XCD groups leave each workgroup too few tiles a level).
+static int group_size(const nk_tuning &t, long long nsources, int cus, int per_xcd) {
+    int gsz = t.group;
+    if (gsz <= 0)
+        for (gsz = 32; gsz > 4 && nsources * gsz > cus;) gsz /= 2;
+    return std::min(gsz, per_xcd);
+}
+
+// Scratch bytes of one group per vertex: path counts, sums, level lists and
+// offsets, degree sums, candidates.
+static const size_t kGroupCell = 8 + 8 + 6 * 4;
+
+bool group_wanted(int32_t n_max, int64_t m_arcs, long long nsources) {
     const nk_tuning t = tuning_get();
     if ((t.flags & 16) || n_max < 1 || t.batch > 1) return false;
     // automatic: sparse graphs of 10^5 to 3 * 10^5 vertices, where sharing
@@ -664,9 +680,32 @@ bool group_wanted(int32_t n_max, int64_t m_arcs) {
     // workgroup (mean-degree-8 random and preferential-attachment graphs);
     // flag bit 3 asks for the group kernel on every graph it can take
     const bool autosel = n_max >= 100000 && n_max <= 300000 && m_arcs <= 12LL * n_max;
-    if (!(t.flags & 8) && !autosel) return false;
     DevInfo di;
     if (dev_info(&di) != NK_OK) return false;
+    // and so are runs with at most half as many sources as compute units,
+    // which leave most of the device idle at one source per workgroup, past
+    // the state-in-LDS kernel's graphs, if launch shape and placement are
+    // left to the library (ms one-source / group: 128 sources, 131,072-vertex
+    // R-MAT 3.6 / 3.0, 5 * 10^5 vertices of mean degree 8 15.5 / 11.6; with 256
+    // sources 3.9 / 4.3 and 20.0 / 20.7).  Below 6 arcs a vertex -- every
+    // planar graph and tree -- levels can be many and narrow, and each costs
+    // a barrier between workgroups; a dense graph that deep has more than
+    // 2^64 paths, or is a chain of cliques (8,750 cliques of 8, 64 sources:
+    // 141 / 171 ms).
+    const bool few = n_max > kStateMax && m_arcs >= 6LL * n_max && 2 * nsources <= di.cus && !(t.flags & 1) &&
+                     t.block == 0 && t.wg_per_cu == 0;
+    if (!(t.flags & 8) && !autosel && !few) return false;
+    if (!(t.flags & 8) && !autosel) {
+        // its scratch, under the limit a one-source launch is cut to
+        size_t avail = (size_t)t.scratch_mib << 20;
+        if (t.scratch_mib <= 0) {
+            size_t fr = 0, tot = 0;
+            if (hipMemGetInfo(&fr, &tot) != hipSuccess) return false;
+            avail = (size_t)((double)(fr + pool_bytes_idle()) * 0.85);
+        }
+        const int groups = di.cus / group_size(t, nsources, di.cus, 32);
+        if ((size_t)groups * ((size_t)n_max + 4096) * kGroupCell > avail) return false;
+    }
     const int block = t.block == 512 ? 512 : 1024;
     hipFuncAttributes attr;
     if (hipFuncGetAttributes(&attr, brandes_group_kernel(block).fn) != hipSuccess) return false;
@@ -674,7 +713,7 @@ bool group_wanted(int32_t n_max, int64_t m_arcs) {
     return attr.sharedSizeBytes + bm <= di.lds_per_block;
 }
 
-nk_status plan_group(int32_t n_max, GroupPlan *gp) {
+nk_status plan_group(int32_t n_max, long long nsources, GroupPlan *gp) {
     DevInfo di;
     nk_status st = dev_info(&di);
     if (st != NK_OK) return st;
@@ -700,17 +739,14 @@ nk_status plan_group(int32_t n_max, GroupPlan *gp) {
     if (hipDeviceGetAttribute(&rate_khz, hipDeviceAttributeWallClockRate, di.device) != hipSuccess || rate_khz < 1)
         rate_khz = 100000;
     (void)hipGetLastError();
-    // workgroups per group: the tuning's, else 4 (measured fastest on the
-    // mid-size graphs; whole-XCD groups leave each workgroup too few tiles
-    // per level)
     const int per_xcd = std::max(1, di.cus * per_cu / nxcc);   // (one XCD has per_cu fewer)
-    int gsz = t.group > 0 ? t.group : 4;
-    if (gsz > per_xcd) gsz = per_xcd;
+    const int gsz = group_size(t, nsources, di.cus, per_xcd);
     gp->gpx = std::max(1, per_xcd / gsz);
     gp->groups = nxcc * gp->gpx;
     gp->nxcc = nxcc;
     gp->stride = (((long long)n_max + 2) + 63) / 64 * 64;
     gp->timeout = (long long)rate_khz * 1000LL * 20LL;   // 20 s
+    gp->reg_wait = gp->timeout;
     gp->lp.mode = kModeBC;
     gp->lp.block = block;
     gp->lp.lds = true;
@@ -735,6 +771,8 @@ nk_status group_alloc(const GroupPlan &gp, Params &p, Scratch &scr) {
     if ((st = scr.get(cells, &p.la)) != NK_OK) return st;
     if ((st = scr.get(cells, &p.ld)) != NK_OK) return st;
     if ((st = scr.get(cells, &p.lvl)) != NK_OK) return st;
+    if ((st = scr.get(cells, &p.ldeg)) != NK_OK) return st;
+    if ((st = scr.get(cells, &p.dacc)) != NK_OK) return st;
     // bottom-up candidates: each member's segment holds the vertices of
     // every G-th bitmap word (G <= 64 members)
     const long long cstride = gp.stride + 64 * 32 + 64;
@@ -749,6 +787,7 @@ nk_status group_alloc(const GroupPlan &gp, Params &p, Scratch &scr) {
     p.xg_groups = gp.groups;
     p.xg_nxcc = gp.nxcc;
     p.xg_timeout = gp.timeout;
+    p.xg_reg_wait = gp.reg_wait;
     p.bu_ratio = tuning_get().bu_ratio;
     p.bw_ratio = tuning_get().bw_ratio;
     return NK_OK;
@@ -756,6 +795,7 @@ nk_status group_alloc(const GroupPlan &gp, Params &p, Scratch &scr) {
 
 nk_status group_enqueue(const GroupPlan &gp, const Params &p, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     NK_HIP(launch_fill_u64(p.sigma, 0ULL, (long long)gp.groups * gp.stride, s));
+    NK_HIP(launch_fill_f64(p.dacc, 0.0, (long long)gp.groups * gp.stride, s));
     NK_HIP(launch_fill_u64(static_cast<unsigned long long *>(p.xg_ctl), 0ULL,
                            (long long)(gp.groups * group_ctl_bytes() / 8), s));
     NK_HIP(launch_fill_u32(p.xg_reg, 0u, 32, s));
@@ -1156,9 +1196,12 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
         }
         // plain and linear-scaling sweeps of undirected graphs without edge
         // scores may run one source per XCD group of workgroups
-        if (!ebc && !dir && est != kEstBisect && group_wanted(n, m)) {
+        if (!ebc && !dir && est != kEstBisect && group_wanted(n, m, k)) {
             GroupPlan gp;
-            if ((st = plan_group(n, &gp)) != NK_OK) return st;
+            if ((st = plan_group(n, k, &gp)) != NK_OK) return st;
+            // a second for the device to clear, then the one-source kernel,
+            // which needs no company
+            gp.reg_wait = gp.timeout / 20;
             Params p;
             memset(&p, 0, sizeof(p));
             p.rowptr = g.rowptr;
@@ -1178,8 +1221,12 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
             NK_HIP(launch_gather_scores(sa, g.perm, scale, bc, s));
             st = finish(dst, h, s);
             NK_HIP(hipEventElapsedTime(&ms, ev0, ev1));
-            stats_record(*h, gp.lp.grid, gp.lp.block, 6, ms);
-            return st;
+            if (h->err != kErrBusy) {
+                stats_record(*h, gp.lp.grid, gp.lp.block, 6, ms);
+                return st;
+            }
+            clear_error();
+            NK_HIP(launch_status_init(dst, s));
         }
         // or several sources per task
         const int msb = (!ebc && !dir && est != kEstBisect) ? ms_batch_for(n, k) : 1;
@@ -1888,7 +1935,7 @@ static nk_status batch_prepare(int32_t G, const int64_t *vtx_off, const int64_t 
             small.push_back(g);
             dyn_max = std::max(dyn_max, by);
             n_small = std::max<int32_t>(n_small, (int32_t)ng);
-        } else if (group_wanted((int32_t)ng, mg)) {
+        } else if (group_wanted((int32_t)ng, mg, kManySources)) {
             grp.push_back(g);
             b->n_group = std::max<int32_t>(b->n_group, (int32_t)ng);
         } else {
@@ -1989,7 +2036,7 @@ static nk_status batch_prepare(int32_t G, const int64_t *vtx_off, const int64_t 
     }
     if (!grp.empty()) {
         if ((st = tables(grp, &b->t_group, &b->o_group, &b->k_group, 1)) != NK_OK) return st;
-        if ((st = plan_group(b->n_group, &b->gplan)) != NK_OK) return st;
+        if ((st = plan_group(b->n_group, kManySources, &b->gplan)) != NK_OK) return st;
         // the group launch has its own scratch; the one-source launch's
         // pointers in b->p stay as they are
         Params gp_params = b->p;

@@ -19,7 +19,8 @@ enum : int32_t {
     kErrGraph = 1,      // CSR structure check failed
     kErrArg = 2,        // a source id or pair index out of range
     kErrOverflow = 4,   // a path count wrapped past 2^64 - 1
-    kErrInternal = 8    // list capacity exceeded (only after a wrap)
+    kErrInternal = 8,   // list capacity exceeded (only after a wrap)
+    kErrBusy = 16       // a group launch's workgroups were not all resident in time: nothing was run
 };
 
 // Per-call device status block: error bits, the dynamic task counter and

@@ -6,11 +6,11 @@
 // its own, 32 workgroups of an XCD keep 32 such arrays live against one
 // 4 MB L2 (and 256 of them against the 256 MB Infinity Cache), and almost
 // every access leaves the XCD.  Here the workgroups of an XCD split into
-// groups of S (a tuning value, 4 by default), each group sharing one
+// groups of S (4 to 32 by the number of sources, or a tuning value), each group sharing one
 // source's arrays: S = 32 keeps a graph of a few hundred thousand vertices
 // in the XCD's L2, smaller groups keep all sources in flight within the
 // Infinity Cache while leaving each member enough of a level to overlap
-// its memory round trips.  The algorithm per source is the same as the
+// its memory round trips (4 where there are sources for all groups).  The algorithm per source is the same as the
 // one-workgroup kernel's (nk_kernels.hip): level-synchronous forward search
 // counting shortest paths (top-down with 64-bit atomics, or bottom-up),
 // then the dependency pull level by level from the deepest (Brandes 2001,
@@ -22,7 +22,10 @@
 // dispatched.  Every workgroup of the launch must be resident at once (the
 // launch is sized to one workgroup per compute unit, all but one compute
 // unit, and made cooperative where the runtime allows); a registration
-// count checks this.  A 1024-thread workgroup holds all of its compute
+// count checks this.  Where another launch holds compute units for longer
+// than the wait, all workgroups leave together before any source is started
+// (one word decides, go or leave), and the caller can run the call on the
+// one-source kernel instead.  A 1024-thread workgroup holds all of its compute
 // unit's vector registers, so the compute unit left free is where the
 // runtime's copy kernels run meanwhile (a progress read during the launch).
 //
@@ -36,8 +39,18 @@
 // within the group, which keeps a barrier near one microsecond.
 //
 // Every wait (registration, group barriers) is bounded by the wall clock;
-// a workgroup that times out raises kErrInternal and the group's abort flag,
-// and every workgroup of the group then leaves its task loop.
+// a workgroup that times out at a barrier raises kErrInternal and the group's
+// abort flag, and every workgroup of the group then leaves its task loop.
+//
+// A call with fewer sources than compute units leaves most of the device
+// idle on the one-source kernel; here S = (compute units / sources) workgroups
+// share one.  ms, one-source kernel against this one: R-MAT scale 18, 16
+// sources 6.3 / 2.0, 64: 6.9 / 3.3, 128: 7.5 / 5.6; scale 20, 64: 31 / 14;
+// 10^6 vertices of mean degree 8, 1 source 20 / 2.8, 64: 31 / 13.  The
+// backward levels that have fewer arcs below than above push, as in the
+// one-source kernel (R-MAT scale 18, 64 sources: 3.9 ms without, 3.3 with;
+// 512 sources: 18.2 and 15.4).  What bounds it then is the depth of the
+// serial chain: levels times a barrier and a few round trips to L2.
 #include "nk_kernels.h"
 
 namespace nk {
@@ -75,6 +88,10 @@ __device__ __forceinline__ uint32_t ldg_u32(const uint32_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+__device__ __forceinline__ double ldg_f64(const double *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __device__ __forceinline__ double f64_of(unsigned long long x) { return __longlong_as_double((long long)x); }
 __device__ __forceinline__ unsigned long long u64_of(double x) { return (unsigned long long)__double_as_longlong(x); }
 
@@ -90,7 +107,7 @@ struct GState {
 };
 
 struct GCount {
-    unsigned long long arcs_fwd, arcs_bwd, dag, reached, tasks, td, bu, arcs_reached;
+    unsigned long long arcs_fwd, arcs_bwd, dag, reached, tasks, td, bu, arcs_reached, bw_push;
 };
 
 // Group barrier.  Contains block barriers: every thread calls it.  Returns
@@ -251,7 +268,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 1) void k_brandes_group(P
     const int tid = threadIdx.x;
     tile_init<BLOCK>(sm);
     GroupCtl *ctls = reinterpret_cast<GroupCtl *>(p.xg_ctl);
-    unsigned int *reg = p.xg_reg;   // [0, 16): workgroups per XCC id; [16]: total
+    unsigned int *reg = p.xg_reg;   // [0, 16): workgroups per XCC id; [16]: total; [17]: go or leave
 
     // registration: group = (dense XCD index, rank modulo groups per XCD)
     if (tid == 0) {
@@ -261,14 +278,25 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 1) void k_brandes_group(P
         const int32_t x = xcc_id();
         const int32_t r = (int32_t)atomicAdd(&reg[x], 1u);
         atomicAdd(&reg[16], 1u);
+        // whoever sees the whole grid registered says go (1), whoever has
+        // waited too long says leave (2); the first word stands for all
         const unsigned long long t0 = wall_clock64();
-        while (ldg_u32(&reg[16]) < gridDim.x) {
-            if ((long long)(wall_clock64() - t0) > p.xg_timeout) {
-                atomicOr(&p.st->err, kErrInternal);
-                gs.flag = 0;
+        uint32_t word = ldg_u32(&reg[17]);
+        while (word == 0u) {
+            const uint32_t want = ldg_u32(&reg[16]) >= gridDim.x                           ? 1u
+                                  : (long long)(wall_clock64() - t0) > p.xg_reg_wait ? 2u
+                                                                                     : 0u;
+            if (want) {
+                word = atomicCAS(&reg[17], 0u, want);
+                if (word == 0u) word = want;
                 break;
             }
             __builtin_amdgcn_s_sleep(2);
+            word = ldg_u32(&reg[17]);
+        }
+        if (word != 1u) {
+            atomicOr(&p.st->err, kErrBusy);
+            gs.flag = 0;
         }
         int32_t xd = 0, distinct = 0;
         for (int32_t i = 0; i < 16; ++i) {
@@ -299,7 +327,9 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 1) void k_brandes_group(P
     int32_t *la = p.la + off;
     int32_t *ld = p.ld + off;
     int32_t *lvl = p.lvl + off;
-    GCount c = {0, 0, 0, 0, 0, 0, 0, 0};
+    int32_t *ldeg = p.ldeg + off;
+    double *dacc = p.dacc + off;
+    GCount c = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     const bool lead = rank == 0;
 
     for (long long it = 0;; ++it) {
@@ -387,7 +417,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 1) void k_brandes_group(P
             GroupLine *acc = &ctl->acc[d & (kAccSlots - 1)];
             const bool bu = (p.bu_ratio > 0.0f) && (mu < (double)p.bu_ratio * mf);
             const int32_t cap = n - f1;
-            if (tid == 0) {
+            if (lead && tid == 0) {
                 if (bu) c.bu++; else c.td++;
             }
             if (tid == 0) gs.dsum = 0ULL;
@@ -518,6 +548,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 1) void k_brandes_group(P
             }
             if (lead && tid == 0) {
                 lvl[d + 2] = f1 + nnew;
+                ldeg[d + 1] = (int32_t)mf_new;
                 c.arcs_reached += (unsigned long long)mf_new;
                 // level d + 2's accumulator (last read two levels ago)
                 GroupLine *nxt = &ctl->acc[(d + 2) & (kAccSlots - 1)];
@@ -555,7 +586,43 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 1) void k_brandes_group(P
             for (int32_t l = Ld - 1; l >= 1; --l) {
                 const int32_t lo = ldg_i32(lvl + l), hi = ldg_i32(lvl + l + 1);
                 const double wfac = p.linear ? (double)l / (double)(l + 1) : 1.0;
-                for (int32_t tb = lo + rank * BLOCK; tb < hi; tb += G * BLOCK) {
+                // whichever side of the level pair has fewer arcs scans them:
+                // the deeper level pushes its coefficients to its marked
+                // (= level l) neighbours' sums
+                const bool push = (double)ldg_i32(ldeg + l + 1) < (double)p.bw_ratio * (double)ldg_i32(ldeg + l);
+                if (push) {
+                    if (lead && tid == 0) c.bw_push++;
+                    const int32_t hi1 = ldg_i32(lvl + l + 2);
+                    for (int32_t tb = hi + rank * BLOCK; tb < hi1; tb += G * BLOCK) {
+                        const int32_t cnt = min(BLOCK, hi1 - tb);
+                        const int32_t total = gstage<BLOCK>(sm, lv, la, ld, sig, tb, cnt);
+                        __syncthreads();
+                        if (tid == 0) c.arcs_bwd += (unsigned long long)total;
+                        for (int32_t rb = 0; rb < total; rb += BLOCK * kGChunk) {
+                            int32_t kk[kGChunk], v[kGChunk];
+                            gchunk<BLOCK>(sm, ci, cnt, total, rb, kk, v);
+                            bool act[kGChunk];
+                            gbits(lbm, v, act);
+#pragma unroll
+                            for (int j = 0; j < kGChunk; ++j)
+                                if ((kk[j] >= 0) & act[j]) atomicAdd(dacc + (uint32_t)v[j], sm.val.f[kk[j]]);
+                        }
+                        __syncthreads();
+                    }
+                    // every member's sums are in before they are taken
+                    if (!group_sync(gs, ctl, p)) {
+                        ok = false;
+                        break;
+                    }
+                    for (int32_t i = lo + rank * BLOCK + tid; i < hi; i += G * BLOCK) {
+                        const int32_t v = ldg_i32(lv + i);
+                        const double sg = (double)ldg_u64(sig + v);
+                        const double delta = sg * ldg_f64(dacc + v) * wfac;
+                        dacc[v] = 0.0;
+                        sig[v] = u64_of((1.0 + delta) / sg);
+                        if (delta != 0.0) atomicAdd(bcg + v, delta);
+                    }
+                } else for (int32_t tb = lo + rank * BLOCK; tb < hi; tb += G * BLOCK) {
                     const int32_t cnt = min(BLOCK, hi - tb);
                     const int32_t total = gstage<BLOCK>(sm, lv, la, ld, sig, tb, cnt);
                     // the rows' path counts move to registers; val takes the sums
@@ -620,6 +687,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 1) void k_brandes_group(P
         atomicAdd(&p.st->stat[kStTd], c.td);
         atomicAdd(&p.st->stat[kStBu], c.bu);
         atomicAdd(&p.st->stat[kStArcsReached], c.arcs_reached);
+        atomicAdd(&p.st->stat[kStBwPush], c.bw_push);
     }
 }
 

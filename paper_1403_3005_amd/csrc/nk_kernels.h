@@ -151,6 +151,7 @@ struct Params {
     void *xg_ctl;
     unsigned int *xg_reg;
     long long xg_timeout;
+    long long xg_reg_wait;
     long long xg_cand_stride;  // per-group entries of the bottom-up candidate array (cand)
     // pair modes: task_list (if not NULL) maps launch task t to sample
     // task_list[t] (outputs indexed by the sample); hashed records: each

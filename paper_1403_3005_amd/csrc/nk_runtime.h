@@ -158,13 +158,17 @@ struct GroupPlan {
     int nxcc;              // XCDs of the device
     long long stride;      // per-group vertex capacity
     long long timeout;     // wall-clock ticks a wait may last
+    long long reg_wait;    // ... and the wait for the whole grid to be resident
 };
 // Whether the group kernel takes a graph of n_max vertices and m_arcs arcs:
 // automatically for sparse graphs of 10^5 to 3 * 10^5 vertices, for every
 // graph under tuning flag bit 3, never under bit 4 or an explicit
 // multi-source batch; and only if its visited bitmap fits LDS.
-bool group_wanted(int32_t n_max, int64_t m_arcs);
-nk_status plan_group(int32_t n_max, GroupPlan *gp);
+// nsources: the sources of the run (a batch, whose graphs share one launch,
+// gives kManySources).
+constexpr long long kManySources = 1LL << 40;
+bool group_wanted(int32_t n_max, int64_t m_arcs, long long nsources);
+nk_status plan_group(int32_t n_max, long long nsources, GroupPlan *gp);
 nk_status group_alloc(const GroupPlan &gp, Params &p, Scratch &scr);
 // Clears the path counts, control blocks and registration counters, then
 // launches (cooperatively unless the stream is being captured).

@@ -265,7 +265,7 @@ nk_status nk_autotune(const int32_t *rowptr, const int32_t *colidx, int32_t n, i
             t.block = 1024;
             t.wg_per_cu = 0;
             tuning_set(t);
-            const bool fits = group_wanted(n, m);
+            const bool fits = group_wanted(n, m, kManySources);
             if (fits && result == NK_OK) trial(t);
         }
     }
