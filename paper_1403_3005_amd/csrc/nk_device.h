@@ -176,6 +176,32 @@ __device__ __forceinline__ void wave_append(bool pred, int32_t value, int32_t *o
     }
 }
 
+// As wave_append for N values a lane, at one LDS atomic a wave.
+template <int N>
+__device__ __forceinline__ void wave_append_all(const bool (&pred)[N], const int32_t (&value)[N], int32_t *out,
+                                                int32_t *counter, int32_t cap, int32_t *err) {
+    int32_t before[N], tot = 0;
+    const unsigned long long below = (1ULL << lane_id()) - 1ULL;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const unsigned long long mask = __ballot(pred[j]);
+        before[j] = tot + (int32_t)__popcll(mask & below);
+        tot += (int32_t)__popcll(mask);
+    }
+    if (tot == 0) return;
+    int32_t base = 0;
+    if (lane_id() == 0) base = atomicAdd(counter, tot);
+    base = __builtin_amdgcn_readfirstlane(base);
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+        if (pred[j]) {
+            if (base + before[j] < cap)
+                out[base + before[j]] = value[j];
+            else
+                atomicOr(err, kErrInternal);
+        }
+}
+
 // As wave_append, and returns the lane's position in `out` (or -1 when
 // pred is false or the position is past cap).
 __device__ __forceinline__ int32_t wave_append_pos(bool pred, int32_t value, int32_t *out, int32_t *counter,
