@@ -275,7 +275,7 @@ static thread_local hipEvent_t t_ev[2] = {nullptr, nullptr};
 DevStatus *host_status() {
     if (!t_host_status) {
         void *p = nullptr;
-        if (hipHostMalloc(&p, sizeof(DevStatus), hipHostMallocDefault) != hipSuccess) {
+        if (hipHostMalloc(&p, sizeof(DevStatus), hipHostMallocPortable) != hipSuccess) {
             (void)hipGetLastError();
             return nullptr;
         }
@@ -298,6 +298,20 @@ nk_status finish(DevStatus *dst, DevStatus *host, hipStream_t s) {
     NK_HIP(hipMemcpyAsync(host, dst, sizeof(DevStatus), hipMemcpyDeviceToHost, s));
     NK_HIP(hipStreamSynchronize(s));
     return map_err(host->err);
+}
+
+// As finish, where the run's last kernel has written the status to the host.
+static nk_status finish_written(const DevStatus *host, hipStream_t s) {
+    NK_HIP(hipStreamSynchronize(s));
+    return map_err(host->err);
+}
+
+static nk_status launch_timed(const LaunchPlan &plan, const Params &p, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+    NK_HIP(hipEventRecord(ev0, s));
+    plan.kernel.launch(dim3(plan.grid), dim3(plan.block), plan.dyn_lds, s, p);
+    NK_HIP(hipGetLastError());
+    NK_HIP(hipEventRecord(ev1, s));
+    return NK_OK;
 }
 
 // Arc indices inside a tile are int32 and run up to 4 * BLOCK past the
@@ -539,11 +553,9 @@ nk_status state_alloc(const StatePlan &sp, Params &p, Scratch &scr) {
     return NK_OK;
 }
 
-nk_status state_enqueue(const StatePlan &sp, const Params &p, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-    if (ev0) NK_HIP(hipEventRecord(ev0, s));
+nk_status state_enqueue(const StatePlan &sp, const Params &p, hipStream_t s) {
     sp.lp.kernel.launch(dim3(sp.lp.grid), dim3(sp.lp.block), sp.lp.dyn_lds, s, p);
     NK_HIP(hipGetLastError());
-    if (ev1) NK_HIP(hipEventRecord(ev1, s));
     return NK_OK;
 }
 
@@ -1087,7 +1099,9 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
     if ((st = scr.get(words, &iso)) != NK_OK) return st;
     DevStatus *h = host_status();
     if (!h) return fail(NK_E_NO_MEMORY, "pinned status buffer");
-    NK_HIP(launch_status_init(dst, s));
+    ScoreAcc sa = {};
+    if (k > 0 && (st = score_acc(n, scr, &sa)) != NK_OK) return st;
+    NK_HIP(launch_run_begin(dst, sa.acc, sa.copies * sa.x, s));
     NK_HIP(launch_validate(rowptr, colidx, n, m, 0, dst, s));
     if (dir && dir->trp) {
         // the in-arcs must be the out-arcs' transpose (checked: structure
@@ -1096,11 +1110,6 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
         if ((st = check_transpose(colidx, n, m, dir->trp, dst, scr, s)) != NK_OK) return st;
     }
     if (k == 0) NK_HIP(launch_fill_f64(bc, 0.0, n, s));
-    ScoreAcc sa;
-    if (k > 0) {
-        if ((st = score_acc(n, scr, &sa)) != NK_OK) return st;
-        NK_HIP(score_clear(sa, s));
-    }
     if (ebc) NK_HIP(launch_fill_f64(ebc, 0.0, m, s));
     LaunchPlan plan = {};
     float ms = 0.0f;
@@ -1121,12 +1130,9 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
         p.linear = est == kEstLinear;
         hipEvent_t ev0, ev1;
         if ((st = thread_events(&ev0, &ev1)) != NK_OK) return st;
-        NK_HIP(hipEventRecord(ev0, s));
-        plan.kernel.launch(dim3(plan.grid), dim3(plan.block), plan.dyn_lds, s, p);
-        NK_HIP(hipGetLastError());
-        NK_HIP(hipEventRecord(ev1, s));
-        NK_HIP(launch_gather_scores(sa, nullptr, scale, bc, s));
-        st = finish(dst, h, s);
+        if ((st = launch_timed(plan, p, s, ev0, ev1)) != NK_OK) return st;
+        NK_HIP(launch_gather_scores(sa, nullptr, scale, bc, s, dst, h));
+        st = finish_written(h, s);
         NK_HIP(hipEventElapsedTime(&ms, ev0, ev1));
         where = 2;
     } else if (k > 0) {
@@ -1187,9 +1193,9 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
             if ((st = state_alloc(sp, p, scr)) != NK_OK) return st;
             hipEvent_t ev0, ev1;
             if ((st = thread_events(&ev0, &ev1)) != NK_OK) return st;
-            if ((st = state_enqueue(sp, p, s, ev0, ev1)) != NK_OK) return st;
-            NK_HIP(launch_gather_scores(sa, g.perm, scale, bc, s));
-            st = finish(dst, h, s);
+            if ((st = launch_timed(sp.lp, p, s, ev0, ev1)) != NK_OK) return st;
+            NK_HIP(launch_gather_scores(sa, g.perm, scale, bc, s, dst, h));
+            st = finish_written(h, s);
             NK_HIP(hipEventElapsedTime(&ms, ev0, ev1));
             stats_record(*h, sp.lp.grid, sp.lp.block, 1, ms);
             return st;
@@ -1218,8 +1224,8 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
             hipEvent_t ev0, ev1;
             if ((st = thread_events(&ev0, &ev1)) != NK_OK) return st;
             if ((st = group_enqueue(gp, p, s, ev0, ev1)) != NK_OK) return st;
-            NK_HIP(launch_gather_scores(sa, g.perm, scale, bc, s));
-            st = finish(dst, h, s);
+            NK_HIP(launch_gather_scores(sa, g.perm, scale, bc, s, dst, h));
+            st = finish_written(h, s);
             NK_HIP(hipEventElapsedTime(&ms, ev0, ev1));
             if (h->err != kErrBusy) {
                 stats_record(*h, gp.lp.grid, gp.lp.block, 6, ms);
@@ -1250,8 +1256,8 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
             hipEvent_t ev0, ev1;
             if ((st = thread_events(&ev0, &ev1)) != NK_OK) return st;
             if ((st = ms_enqueue(mp, p, s, ev0, ev1)) != NK_OK) return st;
-            NK_HIP(launch_gather_scores(sa, g.perm, scale, bc, s));
-            st = finish(dst, h, s);
+            NK_HIP(launch_gather_scores(sa, g.perm, scale, bc, s, dst, h));
+            st = finish_written(h, s);
             NK_HIP(hipEventElapsedTime(&ms, ev0, ev1));
             stats_record(*h, mp.lp.grid, mp.lp.block, 4, ms);
             stats_set_batch(msb);
@@ -2079,7 +2085,7 @@ static nk_status batch_enqueue(const BatchSetup &b, hipStream_t s, hipEvent_t ev
         q.g_task = sq.t;
         q.g_order = sq.o;
         q.ntasks = sq.k;
-        nk_status st = state_enqueue(sq.plan, q, s, nullptr, nullptr);
+        nk_status st = state_enqueue(sq.plan, q, s);
         if (st != NK_OK) return st;
     }
     if (b.g_large > 0) {

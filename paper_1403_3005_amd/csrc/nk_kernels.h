@@ -217,6 +217,8 @@ hipError_t launch_edge_symmetrize(const int32_t *rowptr, const int32_t *colidx, 
 
 // Small helper launches (all asynchronous on `s`).
 hipError_t launch_status_init(DevStatus *st, hipStream_t s);
+// The same and zeros in x[0, count), in one launch.
+hipError_t launch_run_begin(DevStatus *st, double *x, long long count, hipStream_t s);
 hipError_t launch_validate(const int32_t *rowptr, const int32_t *colidx, int32_t n, int64_t m, int32_t strict,
                            DevStatus *st, hipStream_t s);
 hipError_t launch_iso_bitmap(const int32_t *rowptr, int32_t n, uint32_t *iso, hipStream_t s);

@@ -51,6 +51,8 @@
 // leaves share the same loop.  Each thread first issues the column loads of its
 // whole chunk, then the bitmap tests, then the path-count atomics or loads,
 // so several global accesses per lane are in flight at once.
+#include <algorithm>
+
 #include "nk_kernels.h"
 
 namespace nk {
@@ -2263,8 +2265,7 @@ KernelRef brandes_kernel(int mode, int block, bool bitmap_in_lds) {
 
 // ---------------------------------------------------------- small kernels --
 
-__global__ void k_status_init(DevStatus *st) {
-    const int t = threadIdx.x;
+__device__ __forceinline__ void status_init(DevStatus *st, int t) {
     if (t == 0) {
         st->err = 0;
         st->pad = 0;
@@ -2274,6 +2275,14 @@ __global__ void k_status_init(DevStatus *st) {
     if (t < kNumPhases) st->cycles[t] = 0ULL;
     if (t < 8) st->sub[t] = 0ULL;
     if (t < 8) st->info[t] = (t == 1) ? 0x7fffffff : 0;
+}
+
+__global__ void k_status_init(DevStatus *st) { status_init(st, threadIdx.x); }
+
+__global__ void k_run_begin(DevStatus *st, double *x, long long count) {
+    if (blockIdx.x == 0) status_init(st, threadIdx.x);
+    const long long stride = (long long)gridDim.x * blockDim.x;
+    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += stride) x[i] = 0.0;
 }
 
 __global__ void k_validate(const int32_t *rowptr, const int32_t *colidx, int32_t n, int64_t m, DevStatus *st) {
@@ -2428,6 +2437,12 @@ hipError_t launch_close_finish(const unsigned long long *acc, const int32_t *per
 
 hipError_t launch_status_init(DevStatus *st, hipStream_t s) {
     hipLaunchKernelGGL(k_status_init, dim3(1), dim3(64), 0, s, st);
+    return hipGetLastError();
+}
+
+hipError_t launch_run_begin(DevStatus *st, double *x, long long count, hipStream_t s) {
+    const long long blocks = std::max(1LL, std::min((count + 255) / 256, 2048LL));
+    hipLaunchKernelGGL(k_run_begin, dim3((unsigned)blocks), dim3(256), 0, s, st, x, count);
     return hipGetLastError();
 }
 

@@ -223,7 +223,7 @@ struct StatePlan {
 bool plan_state(int32_t n_max, long long ntasks, StatePlan *sp);
 // Scratch of the launch, and the launch.
 nk_status state_alloc(const StatePlan &sp, Params &p, Scratch &scr);
-nk_status state_enqueue(const StatePlan &sp, const Params &p, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
+nk_status state_enqueue(const StatePlan &sp, const Params &p, hipStream_t s);
 
 // Allocates per-slot scratch for `plan`, clears the path counts, fills the
 // scratch fields of `p` and launches the persistent kernel on `s`,
@@ -288,8 +288,10 @@ struct ScoreAcc {
 nk_status score_acc(long long n, Scratch &scr, ScoreAcc *a);
 void score_params(const ScoreAcc &a, Params *p);
 hipError_t score_clear(const ScoreAcc &a, hipStream_t s);
-// out[v] = scale * sum of the copies at perm[v] (v where perm is NULL)
-hipError_t launch_gather_scores(const ScoreAcc &a, const int32_t *perm, double scale, double *out, hipStream_t s);
+// out[v] = scale * sum of the copies at perm[v] (v where perm is NULL); with
+// host, also *host = *st (pinned memory; read it after the stream is done).
+hipError_t launch_gather_scores(const ScoreAcc &a, const int32_t *perm, double scale, double *out, hipStream_t s,
+                                const DevStatus *st = nullptr, DevStatus *host = nullptr);
 hipError_t launch_gather_u32(const uint32_t *in, const int32_t *perm, int32_t n, uint32_t *out, hipStream_t s);
 
 // Vertex-diameter bound (see nk_vd_bound); runs synchronously on `s`.
