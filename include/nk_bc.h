@@ -517,8 +517,9 @@ nk_status nk_get_tuning(nk_tuning *t);
  * on the one-source kernel (flags bit 4), then from the fastest of those
  * one resident workgroup per compute unit, batch = 4, 8 and 16 sources per
  * task (block 1024) and, where its bitmap fits LDS, the group kernel
- * (flags bit 3) with group = 2, 4 and 8 workgroups per source, and returns
- * the fastest in *best (HOST).  The current tuning is left unchanged.  If
+ * (flags bit 3) with group = 2, 4 and 8 workgroups per source, those
+ * compared with the fastest of the others on the sample repeated to
+ * sixteen sources per compute unit, and returns the fastest in *best (HOST).  The current tuning is left unchanged.  If
  * cache_path is not NULL the winner is stored there under the graph's
  * shape bucket (floor log2 n, round log2 mean degree, round log2 max
  * degree / mean degree) in a flat JSON object

@@ -206,15 +206,17 @@ nk_status nk_autotune(const int32_t *rowptr, const int32_t *colidx, int32_t n, i
         ~TrialScope() { t_trials = false; }
     } trials;
     // times one setting: an untimed run (allocation, caches), then the timed one
+    const int32_t *ts = sources;
+    int32_t tk = k;
     auto trial = [&](const nk_tuning &t) -> bool {
         tuning_set(t);
-        st = nk_bc_sources(rowptr, colidx, n, m, sources, k, 1.0, bc, stream);
+        st = nk_bc_sources(rowptr, colidx, n, m, ts, tk, 1.0, bc, stream);
         if (st != NK_OK) {
             result = st;
             return false;
         }
         const auto t0 = std::chrono::steady_clock::now();
-        st = nk_bc_sources(rowptr, colidx, n, m, sources, k, 1.0, bc, stream);
+        st = nk_bc_sources(rowptr, colidx, n, m, ts, tk, 1.0, bc, stream);
         const double ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
         if (st != NK_OK) {
             result = st;
@@ -257,16 +259,46 @@ nk_status nk_autotune(const int32_t *rowptr, const int32_t *colidx, int32_t n, i
             if (result == NK_OK) trial(t);
         }
         // the group kernel with 2, 4 and 8 workgroups per source, where its
-        // visited bitmap fits LDS
-        for (int g : {2, 4, 8}) {
-            t = base;
-            t.flags = (saved.flags & ~24) | 8;
-            t.group = g;
-            t.block = 1024;
-            t.wg_per_cu = 0;
-            tuning_set(t);
-            const bool fits = group_wanted(n, m, kManySources);
-            if (fits && result == NK_OK) trial(t);
+        // visited bitmap fits LDS.  A sample of few sources leaves compute
+        // units idle at one source per workgroup and the group kernel wins
+        // on that alone (R-MAT scale 20, 256 sources: 40 ms against 36; 4096:
+        // 423 against 480), so the two are compared on the sample repeated
+        // to sixteen sources a compute unit.
+        t = base;
+        t.flags = (saved.flags & ~24) | 8;
+        tuning_set(t);
+        DevInfo di;
+        int32_t *wide = nullptr;
+        if (result == NK_OK && group_wanted(n, m, kManySources) && dev_info(&di) == NK_OK) {
+            const nk_tuning one = win;
+            const double one_ms = best_ms;
+            const int32_t reps = k < 16 * di.cus ? (16 * di.cus + k - 1) / k : 1;
+            if (reps > 1) {
+                hipError_t e = hipMalloc((void **)&wide, sizeof(int32_t) * (size_t)k * reps);
+                for (int32_t r = 0; r < reps && e == hipSuccess; ++r)
+                    e = hipMemcpyAsync(wide + (size_t)r * k, sources, sizeof(int32_t) * (size_t)k,
+                                       hipMemcpyDeviceToDevice, s);
+                if (e != hipSuccess) {
+                    (void)hipGetLastError();
+                    result = fail(NK_E_NO_MEMORY, "autotuner: sources of the repeated sample");
+                } else {
+                    ts = wide;
+                    tk = k * reps;
+                    best_ms = 1e300;
+                    trial(one);
+                }
+            }
+            for (int g : {2, 4, 8}) {
+                t = base;
+                t.flags = (saved.flags & ~24) | 8;
+                t.group = g;
+                t.block = 1024;
+                t.wg_per_cu = 0;
+                if (result == NK_OK) trial(t);
+            }
+            // the time of the sample itself
+            if (reps > 1) best_ms = win.flags & 8 ? best_ms / reps : one_ms;
+            if (wide) (void)hipFree(wide);
         }
     }
     tuning_set(saved);
