@@ -471,6 +471,9 @@ nk_status nk_last_stats(int64_t *out);
  *              one record per vertex -- which it does by itself when records
  *              per vertex (68 bytes per vertex per slot) would leave fewer
  *              slots than compute units in half the device memory;
+ *              bit 7: the workgroups of a single-graph call's group launch
+ *              leave as if another launch held the device, and the call goes
+ *              on to the other kernels (for testing that way);
  *   bw_ratio   in the dependency sweep, handle level l by pushing from level
  *              l+1 when the arcs of level l+1 are below bw_ratio x the arcs
  *              of level l (0 = always pull; default 0.1);

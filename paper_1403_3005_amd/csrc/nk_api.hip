@@ -1207,7 +1207,7 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
             if ((st = plan_group(n, k, &gp)) != NK_OK) return st;
             // a second for the device to clear, then the one-source kernel,
             // which needs no company
-            gp.reg_wait = gp.timeout / 20;
+            gp.reg_wait = (tuning_get().flags & 128) ? -1 : gp.timeout / 20;
             Params p;
             memset(&p, 0, sizeof(p));
             p.rowptr = g.rowptr;

@@ -283,9 +283,9 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 1) void k_brandes_group(P
         const unsigned long long t0 = wall_clock64();
         uint32_t word = ldg_u32(&reg[17]);
         while (word == 0u) {
-            const uint32_t want = ldg_u32(&reg[16]) >= gridDim.x                           ? 1u
-                                  : (long long)(wall_clock64() - t0) > p.xg_reg_wait ? 2u
-                                                                                     : 0u;
+            const uint32_t want = p.xg_reg_wait >= 0 && ldg_u32(&reg[16]) >= gridDim.x ? 1u
+                                  : (long long)(wall_clock64() - t0) > p.xg_reg_wait   ? 2u
+                                                                                       : 0u;
             if (want) {
                 word = atomicCAS(&reg[17], 0u, want);
                 if (word == 0u) word = want;
@@ -295,26 +295,28 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 1) void k_brandes_group(P
             word = ldg_u32(&reg[17]);
         }
         if (word != 1u) {
+            // (the counts below are complete only once all have registered)
             atomicOr(&p.st->err, kErrBusy);
             gs.flag = 0;
-        }
-        int32_t xd = 0, distinct = 0;
-        for (int32_t i = 0; i < 16; ++i) {
-            const bool used = ldg_u32(&reg[i]) > 0u;
-            if (i < x) xd += used ? 1 : 0;
-            distinct += used ? 1 : 0;
-        }
-        const int32_t cnt = (int32_t)ldg_u32(&reg[x]);
-        const int32_t gpx = p.xg_gpx;
-        const int32_t sub = r % gpx;
-        gs.group = xd * gpx + sub;
-        gs.rank = r / gpx;
-        gs.gsize = (cnt - sub + gpx - 1) / gpx;
-        // (candidate segments are sized for at most 64 members; a group must
-        // not span XCDs, so every XCD the device has must report its own id)
-        if (gs.group >= p.xg_groups || gs.gsize > 64 || distinct != p.xg_nxcc) {
-            atomicOr(&p.st->err, kErrInternal);
-            gs.flag = 0;
+        } else {
+            int32_t xd = 0, distinct = 0;
+            for (int32_t i = 0; i < 16; ++i) {
+                const bool used = ldg_u32(&reg[i]) > 0u;
+                if (i < x) xd += used ? 1 : 0;
+                distinct += used ? 1 : 0;
+            }
+            const int32_t cnt = (int32_t)ldg_u32(&reg[x]);
+            const int32_t gpx = p.xg_gpx;
+            const int32_t sub = r % gpx;
+            gs.group = xd * gpx + sub;
+            gs.rank = r / gpx;
+            gs.gsize = (cnt - sub + gpx - 1) / gpx;
+            // (candidate segments are sized for at most 64 members; a group must
+            // not span XCDs, so every XCD the device has must report its own id)
+            if (gs.group >= p.xg_groups || gs.gsize > 64 || distinct != p.xg_nxcc) {
+                atomicOr(&p.st->err, kErrInternal);
+                gs.flag = 0;
+            }
         }
     }
     __syncthreads();

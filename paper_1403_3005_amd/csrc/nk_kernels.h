@@ -141,9 +141,10 @@ struct Params {
     // group mode (nk_group.hip): the workgroups of one XCD share a source;
     // per group (not per slot) `stride` elements of sigma, lv, la, ld, lvl;
     // xg_gpx groups per XCD, xg_groups groups allocated, their control
-    // blocks (group_ctl_bytes() each, zeroed before the launch), 17
-    // registration counters (zeroed), and the longest wait allowed, in
-    // wall-clock ticks
+    // blocks (group_ctl_bytes() each, zeroed before the launch), 18
+    // registration words (zeroed), and the longest waits allowed at a
+    // barrier and for the whole grid to register (negative: leave at once),
+    // in wall-clock ticks
     int32_t xg_gpx;
     int32_t xg_groups;
     int32_t xg_nxcc;           // XCDs of the device (each must hold workgroups of the launch)
