@@ -43,6 +43,10 @@ constexpr int kWaveRow = 64;
 constexpr int kBlockRow = 512;
 constexpr int kCloseDeep = 96;                   // levels run before giving up
 constexpr int kListBlocks = 2048;                // blocks that take each list, at most
+// A launch holds less than 2^32 threads (a larger one runs nothing and
+// reports nothing), and a level takes four threads a vertex.
+constexpr int32_t kCloseMax = 1 << 29;
+static_assert((kCloseMax / kVerts + 2LL * kListBlocks) * kCloseBlock < 1LL << 32, "threads of a level");
 
 struct CloseArgs {
     const int32_t *rp;
@@ -365,6 +369,7 @@ nk_status close_bits(const int32_t *rowptr, const int32_t *colidx, int32_t n, in
     // preparation: small calls stay there (G(300, 900), 100 sources: 142 us
     // there, 196 here; G(5000, 5000) exact: 1.8 and 3.3 ms; BA-9973, 64
     // sources: 513 and 190 us; exact: 3.7 and 2.2 ms).
+    if (n > kCloseMax) return NK_OK;
     const bool one_pass = k <= 1024;
     if (one_pass ? (double)k * (double)m < 2e6 : m < 20000) return NK_OK;
     int W = 1;
