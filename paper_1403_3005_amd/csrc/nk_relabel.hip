@@ -209,7 +209,25 @@ nk_status score_acc(long long n, Scratch &scr, ScoreAcc *a) {
     a->copies = n <= kScoreCopiesMax ? kScoreCopies : 1;
     a->x = (n + 31) / 32 * 32;   // whole lines
     a->n = n;
-    return scr.get(a->copies * a->x, &a->acc);
+    const long long bytes = 8 * a->copies * a->x;
+    if (a->copies > 1 && bytes > kScoreCopiesFree) {
+        // many copies of many scores: only beside plenty of memory
+        const int32_t cap_mib = tuning_get().scratch_mib;
+        size_t avail = (size_t)cap_mib << 20;
+        if (cap_mib <= 0) {
+            size_t fr = 0, tot = 0;
+            NK_HIP(hipMemGetInfo(&fr, &tot));
+            avail = (fr + pool_bytes_idle()) / 8;
+        }
+        if ((size_t)bytes > avail) a->copies = 1;
+    }
+    nk_status st = scr.get(a->copies * a->x, &a->acc);
+    if (st != NK_OK && a->copies > 1) {
+        clear_error();
+        a->copies = 1;
+        st = scr.get(a->x, &a->acc);
+    }
+    return st;
 }
 
 void score_params(const ScoreAcc &a, Params *p) {

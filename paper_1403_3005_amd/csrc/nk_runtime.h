@@ -277,9 +277,13 @@ hipError_t launch_arcs_back(const double *in, const int32_t *rp_new, const int32
                             int32_t n, double *out, hipStream_t s);
 // Score accumulators of a run over n vertices (all graphs of a batch
 // together): one copy per XCD up to 2^25 vertices (8 x 8 bytes a vertex),
-// a single shared one above.
+// a single shared one above, and where the copies of more than half a million
+// vertices (kScoreCopiesFree bytes) pass the tuning's scratch cap or, with
+// none set, an eighth of the device memory that is free or idle in the pool:
+// the slots' scratch matters more than the copies.
 constexpr int kScoreCopies = 8;
 constexpr long long kScoreCopiesMax = 1LL << 25;
+constexpr long long kScoreCopiesFree = 32LL << 20;
 struct ScoreAcc {
     double *acc;
     long long n, x;        // vertices; doubles from one copy to the next
