@@ -522,7 +522,16 @@ bool plan_state(int32_t n_max, long long ntasks, StatePlan *sp) {
     if (t.wg_per_cu > 0 && t.wg_per_cu < occ) occ = t.wg_per_cu;
     const long long stride = (((long long)n_max + 2) + 63) / 64 * 64;
     long long grid = std::min<long long>((long long)di.cus * occ, ntasks);
-    if (cold && t.scratch_mib > 0) grid = std::min<long long>(grid, ((long long)t.scratch_mib << 20) / (stride * 12));
+    if (cold) {
+        // as plan_launch: the grid is cut to the slots that fit
+        size_t avail = (size_t)t.scratch_mib << 20;
+        if (t.scratch_mib <= 0) {
+            size_t fr = 0, tot = 0;
+            if (hipMemGetInfo(&fr, &tot) != hipSuccess) return false;
+            avail = (size_t)((double)(fr + pool_bytes_idle()) * 0.85);
+        }
+        grid = std::min<long long>(grid, (long long)(avail / ((size_t)stride * 12)));
+    }
     if (grid < 1) return false;
     sp->cold = cold;
     sp->hot = hot;

@@ -25,8 +25,13 @@ def _leave(mib):
     """Takes all device memory but `mib` MiB."""
     nk.nk_shutdown()
     torch.cuda.empty_cache()
-    free = torch.cuda.mem_get_info()[0]
-    return torch.empty(free - (mib << 20), dtype=torch.uint8, device="cuda")
+    taken = []
+    for _ in range(3):                                     # (a large allocation can leave more than was asked for)
+        free = torch.cuda.mem_get_info()[0] - (mib << 20)
+        if free > 2 << 20:
+            taken.append(torch.empty(free, dtype=torch.uint8, device="cuda"))
+    assert torch.cuda.mem_get_info()[0] <= (mib + 32) << 20
+    return taken
 
 
 def test_copies_of_the_scores():
@@ -45,3 +50,21 @@ def test_copies_of_the_scores():
     assert bc[leaves].item() == leaves - 1                 # the star's centre, from leaf 0
     bc[leaves] = 0.0
     assert int(torch.count_nonzero(bc)) == 0
+
+
+def test_state_in_lds():
+    """Up to 65,534 vertices part of a slot's state is in device memory, 200 MB
+    for a slot on every compute unit; with less the grid shrinks."""
+    g = gg.barabasi_albert(65000, 4, 3)
+    rp, ci = upload(g)
+    src = gg.sample_sources(g.n, 600, 4)
+    ref = oracle.bc_sources(g.rowptr, g.colidx, src, 1.0, nthreads=16)
+    assert_scores_close(nk.nk_bc_sources(rp, ci, ivec(src), 1.0).cpu().numpy(), ref, "memory at hand")
+    grid = nk.nk_last_stats()["workgroups"]
+    s, bc = ivec(src), torch.empty(g.n, dtype=torch.float64, device="cuda")
+    taken = _leave(128)
+    nk.nk_bc_sources(rp, ci, s, 1.0, bc=bc)
+    st = nk.nk_last_stats()
+    del taken
+    assert st["bitmap_lds"] == 1 and 0 < st["workgroups"] < grid
+    assert_scores_close(bc.cpu().numpy(), ref, "128 MiB left")
