@@ -79,6 +79,24 @@ struct PoolBlock {
 static std::mutex g_pool_mu;
 static std::vector<PoolBlock> g_pool;
 
+void pool_trim() {
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    std::vector<void *> idle;
+    {
+        std::lock_guard<std::mutex> lk(g_pool_mu);
+        for (size_t i = 0; i < g_pool.size();) {
+            if (!g_pool[i].busy && g_pool[i].device == dev) {
+                idle.push_back(g_pool[i].ptr);
+                g_pool.erase(g_pool.begin() + i);
+            } else {
+                ++i;
+            }
+        }
+    }
+    for (void *q : idle) (void)hipFree(q);
+}
+
 nk_status Scratch::get(size_t bytes, void **out) {
     int dev = 0;
     NK_HIP(hipGetDevice(&dev));
@@ -104,19 +122,7 @@ nk_status Scratch::get(size_t bytes, void **out) {
     if (e != hipSuccess) {
         (void)hipGetLastError();
         // release idle blocks of this device and retry once
-        std::vector<void *> idle;
-        {
-            std::lock_guard<std::mutex> lk(g_pool_mu);
-            for (size_t i = 0; i < g_pool.size();) {
-                if (!g_pool[i].busy && g_pool[i].device == dev) {
-                    idle.push_back(g_pool[i].ptr);
-                    g_pool.erase(g_pool.begin() + i);
-                } else {
-                    ++i;
-                }
-            }
-        }
-        for (void *q : idle) (void)hipFree(q);
+        pool_trim();
         e = hipMalloc(&p, bytes);
         if (e != hipSuccess) {
             (void)hipGetLastError();
@@ -1511,13 +1517,15 @@ static nk_status closeness_impl(const int32_t *rowptr, const int32_t *colidx, in
     LaunchPlan plan = {};
     float ms = 0.0f;
     if (k > 0) {
-        // bit-parallel searches, unless memory or depth rule them out
+        // bit-parallel searches, unless memory or depth rule them out (their
+        // scratch has gone back then, before the other kernel sizes its own)
+        Scratch bits;
         hipEvent_t ev0, ev1;
         if ((st = thread_events(&ev0, &ev1)) != NK_OK) return st;
         NK_HIP(hipEventRecord(ev0, s));
         bool done = false;
         int levels = 0;
-        if ((st = close_bits(rowptr, colidx, n, m, sources, k, sampled, out, dst, scr, s, &done, &levels)) != NK_OK)
+        if ((st = close_bits(rowptr, colidx, n, m, sources, k, sampled, out, dst, bits, s, &done, &levels)) != NK_OK)
             return st;
         NK_HIP(hipEventRecord(ev1, s));
         if (done) {

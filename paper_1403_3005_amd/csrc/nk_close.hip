@@ -455,7 +455,14 @@ nk_status close_bits(const int32_t *rowptr, const int32_t *colidx, int32_t n, in
             NK_HIP(hipStreamSynchronize(s));
             for (unsigned long long x : last) any |= x;
             if (!any) break;
-            if (launched == kCloseDeep) return NK_OK;   // too deep: the caller's other kernel
+            if (launched == kCloseDeep) {
+                // too deep: the caller's other kernel.  The stream is done with
+                // the bits; where they are much of the memory at hand, the pool
+                // does not keep them in their sizes either
+                scr.release_all();
+                if (need(W) > avail / 8) pool_trim();
+                return NK_OK;
+            }
         }
         guess = launched;
         *levels += launched;

@@ -65,6 +65,7 @@ private:
     std::vector<void *> held_;
 };
 void pool_clear();
+void pool_trim();           // frees the current device's idle blocks
 size_t pool_bytes_in_use();
 size_t pool_bytes_idle();   // idle pooled bytes on the current device
 
@@ -199,8 +200,8 @@ nk_status largest_unreached_component(const int32_t *rowptr, const int32_t *coli
 // Closeness by bit-parallel searches, up to 1024 sources a pass
 // (nk_close.hip): exact (sources NULL, k = n) or sampled scores into out.
 // *done = false (nothing written but scratch and, for a source out of
-// range, the status) where the bits do not fit the scratch or the graph has
-// too many levels.  *levels: levels run.
+// range, the status; scr empty again) where the bits do not fit the scratch
+// or the graph has too many levels.  *levels: levels run.
 nk_status close_bits(const int32_t *rowptr, const int32_t *colidx, int32_t n, int64_t m, const int32_t *sources,
                      int32_t k, bool sampled, double *out, DevStatus *dst, Scratch &scr, hipStream_t s, bool *done,
                      int *levels);

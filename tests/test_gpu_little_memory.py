@@ -68,3 +68,21 @@ def test_state_in_lds():
     del taken
     assert st["bitmap_lds"] == 1 and 0 < st["workgroups"] < grid
     assert_scores_close(bc.cpu().numpy(), ref, "128 MiB left")
+
+
+def test_closeness_that_gives_up():
+    """A path of 200 vertices beside a star and isolated vertices, 10^6 in all,
+    has too many levels for the bit-parallel searches; their 400 MB of bits do
+    not count against the kernel that takes over (44 MB a slot)."""
+    g = gg.disjoint_union([gg.path(200), gg.star(5200), gg.from_edges(994_600, [], [])])
+    rp, ci = upload(g)
+    src = np.concatenate([np.arange(200), np.arange(200, 1024) + 3000])
+    ref, _ = oracle.closeness_approx(g.rowptr, g.colidx, src)
+    s, out = ivec(src), torch.empty(g.n, dtype=torch.float64, device="cuda")
+    nk.nk_closeness_sampled(rp, ci, s, out=out)            # with memory at hand
+    taken = _leave(650)
+    nk.nk_closeness_sampled(rp, ci, s, out=out)
+    st = nk.nk_last_stats()
+    del taken
+    assert st["reached"] > 0 and 6 <= st["workgroups"] < 20, st
+    assert np.allclose(out.cpu().numpy(), ref, rtol=1e-14, atol=0.0)
