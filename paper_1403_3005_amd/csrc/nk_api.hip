@@ -1523,9 +1523,10 @@ static nk_status closeness_impl(const int32_t *rowptr, const int32_t *colidx, in
         hipEvent_t ev0, ev1;
         if ((st = thread_events(&ev0, &ev1)) != NK_OK) return st;
         NK_HIP(hipEventRecord(ev0, s));
-        bool done = false;
+        bool done = false, deep = false;
         int levels = 0;
-        if ((st = close_bits(rowptr, colidx, n, m, sources, k, sampled, out, dst, bits, s, &done, &levels)) != NK_OK)
+        if ((st = close_bits(rowptr, colidx, n, m, sources, k, sampled, out, dst, bits, s, &done, &deep, &levels)) !=
+            NK_OK)
             return st;
         NK_HIP(hipEventRecord(ev1, s));
         if (done) {
@@ -1550,7 +1551,8 @@ static nk_status closeness_impl(const int32_t *rowptr, const int32_t *colidx, in
             if ((st = scr.get(n, &acc)) != NK_OK) return st;
             NK_HIP(launch_fill_u64(acc, 0ULL, n, s));
         }
-        if ((st = plan_launch(kModeClose, n, k, 0, &plan, m)) != NK_OK) return st;
+        // (a deep graph is a thin one more often than not: narrow workgroups)
+        if ((st = plan_launch(kModeClose, n, k, 0, &plan, deep ? 0 : m)) != NK_OK) return st;
         Params p;
         memset(&p, 0, sizeof(p));
         p.rowptr = g.rowptr;

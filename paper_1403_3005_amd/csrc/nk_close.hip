@@ -20,8 +20,8 @@
 // are 0.24 each; 12.9 ms with one workgroup per search, which reads every arc
 // once per source.
 //
-// A level is a launch, so graphs of many levels (kCloseDeep) go to the
-// one-workgroup-per-source kernel instead, whose levels cost it less.
+// A level is a launch, so graphs of many levels go to the one-workgroup-per-
+// source kernel instead, whose levels cost it less (close_grows, kCloseDeep).
 #include <string.h>
 
 #include <algorithm>
@@ -41,7 +41,12 @@ constexpr int kVerts = 64;                       // vertices of a block
 // of them among its own vertices took 5 of a level's 6 ms.
 constexpr int kWaveRow = 64;
 constexpr int kBlockRow = 512;
-constexpr int kCloseDeep = 96;                   // levels run before giving up
+constexpr int kCloseDeep = 96;                   // levels the first pass may take
+constexpr int kCloseFirst = 6;                   // levels before the first look at them
+constexpr int kCloseRows = 128;                  // levels whose masks and counters are kept
+constexpr int kCloseXcd = 8;                     // counter lines a level
+constexpr int kCloseRow = 16 * (1 + kCloseXcd);  // words a level: masks, counters
+enum CloseCount { kCcPairs = 0, kCloseCount };   // new (source, vertex) pairs
 constexpr int kListBlocks = 2048;                // blocks that take each list, at most
 // A launch holds less than 2^32 threads (a larger one runs nothing and
 // reports nothing), and a level takes four threads a vertex.
@@ -59,7 +64,9 @@ struct CloseArgs {
     uint32_t *act_next;              // clear
     uint32_t *act_clear;             // to clear for the level after
     unsigned long long *acc;         // distance sums
-    unsigned long long *alive;       // 16 words a level: the sources that reached something there
+    const unsigned long long *alive_prev;   // 16 words: the sources that reached something on the last level
+    unsigned long long *alive;       // ... on this one (clear)
+    unsigned long long *counts;      // this level's counters, a line per XCD (kCloseCount of them)
     const int32_t *list[2];          // rows for a wave, for a block
     const int32_t *nlist;            // their counts
     int32_t level;
@@ -102,10 +109,17 @@ __device__ __forceinline__ unsigned long long or_heads(const CloseArgs &a, int32
     return r;
 }
 
+// What a block adds up in LDS before it goes to the level's words.
+template <int W>
+struct CloseSums {
+    unsigned long long alive[W];
+    unsigned long long count[kCloseCount];
+};
+
 // New bits of vertex v (word `word` of them in this lane, slot 0 counts):
 // stored, added to the distance sum; true if there are any.
 template <int W>
-__device__ __forceinline__ bool settle(const CloseArgs &a, unsigned long long *alive, int32_t v, int gl,
+__device__ __forceinline__ bool settle(const CloseArgs &a, CloseSums<W> &sums, int32_t v, int gl,
                                        unsigned long long seen, unsigned long long fresh) {
     const int word = gl % W;
     const bool mine = gl < W;
@@ -116,28 +130,34 @@ __device__ __forceinline__ bool settle(const CloseArgs &a, unsigned long long *a
     if (mine) {
         a.next[(long long)v * W + word] = fresh;
         a.seen[(long long)v * W + word] = seen | fresh;
-        if (fresh) atomicOr(&alive[word], fresh);
+        if (fresh) atomicOr(&sums.alive[word], fresh);
     }
-    if (gl == 0) a.acc[v] += (unsigned long long)a.level * (unsigned long long)c;
+    if (gl == 0) {
+        a.acc[v] += (unsigned long long)a.level * (unsigned long long)c;
+        atomicAdd(&sums.count[kCcPairs], (unsigned long long)c);
+    }
     return true;
 }
 
 // The block's searches that reached something, added to the level's mask
 // (read first: most blocks bring nothing new, and adds to the one line by all
-// XCDs are slow).
+// XCDs are slow), and its counts, to its XCD's line.
 template <int W>
-__device__ __forceinline__ void alive_out(const CloseArgs &a, const unsigned long long *alive) {
+__device__ __forceinline__ void sums_out(const CloseArgs &a, CloseSums<W> &sums) {
     __syncthreads();
     if (threadIdx.x < W) {
-        unsigned long long *al = a.alive + a.level * 16 + threadIdx.x;
-        const unsigned long long x = alive[threadIdx.x];
+        unsigned long long *al = a.alive + threadIdx.x;
+        const unsigned long long x = sums.alive[threadIdx.x];
         if (x & ~__hip_atomic_load(al, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicOr(al, x);
+    } else if (threadIdx.x >= kWave && threadIdx.x < kWave + kCloseCount) {
+        const int i = threadIdx.x - kWave;
+        if (sums.count[i]) atomicAdd(a.counts + (xcc_id() & (kCloseXcd - 1)) * 16 + i, sums.count[i]);
     }
 }
 
 template <int W>
 __global__ __launch_bounds__(kCloseBlock) void k_close_level(CloseArgs a) {
-    __shared__ unsigned long long alive[W];
+    __shared__ CloseSums<W> sums;
     __shared__ uint32_t bits[kVerts / 32];
     __shared__ unsigned long long part[W];
     __shared__ int32_t stop;
@@ -145,16 +165,17 @@ __global__ __launch_bounds__(kCloseBlock) void k_close_level(CloseArgs a) {
     {
         // no search left: nothing to do
         unsigned long long left = 0ULL;
-        for (int w = 0; w < W; ++w) left |= a.alive[(a.level - 1) * 16 + w];
+        for (int w = 0; w < W; ++w) left |= a.alive_prev[w];
         if (left == 0ULL) return;
     }
     const int tid = threadIdx.x, lane = lane_id();
     const int gl = tid % kLanes, word = gl % W;
     // the searches still going: those that reached something on the last
     // level (the bits of the others are not looked for)
-    const unsigned long long full = a.alive[(a.level - 1) * 16 + word];
+    const unsigned long long full = a.alive_prev[word];
     int32_t blk = (int32_t)blockIdx.x;
-    if (tid < W) alive[tid] = 0ULL;
+    if (tid < W) sums.alive[tid] = 0ULL;
+    if (tid < kCloseCount) sums.count[tid] = 0ULL;
     __syncthreads();
 
     if (blk < a.big_blocks) {
@@ -185,13 +206,13 @@ __global__ __launch_bounds__(kCloseBlock) void k_close_level(CloseArgs a) {
             }
             if (tid < kWave) {
                 // the first group settles
-                const bool fresh = settle<W>(a, alive, v, lane < kLanes ? gl : kLanes, seen,
+                const bool fresh = settle<W>(a, sums, v, lane < kLanes ? gl : kLanes, seen,
                                              lane < kLanes ? got & full & ~seen : 0ULL);
                 if (lane == 0 && fresh) atomicOr(&a.act_next[v >> 5], 1u << (v & 31));
             }
             __syncthreads();
         }
-        alive_out<W>(a, alive);
+        sums_out<W>(a, sums);
         return;
     }
     blk -= a.big_blocks;
@@ -215,11 +236,11 @@ __global__ __launch_bounds__(kCloseBlock) void k_close_level(CloseArgs a) {
                 if (__ballot((full & ~(seen | got)) != 0ULL) == 0ULL) break;
                 u = u1;
             }
-            const bool fresh = settle<W>(a, alive, v, lane < kLanes ? gl : kLanes, seen,
+            const bool fresh = settle<W>(a, sums, v, lane < kLanes ? gl : kLanes, seen,
                                          lane < kLanes ? got & full & ~seen : 0ULL);
             if (lane == 0 && fresh) atomicOr(&a.act_next[v >> 5], 1u << (v & 31));
         }
-        alive_out<W>(a, alive);
+        sums_out<W>(a, sums);
         return;
     }
     blk -= a.wave_blocks;
@@ -252,11 +273,11 @@ __global__ __launch_bounds__(kCloseBlock) void k_close_level(CloseArgs a) {
             u = u1;
         }
         got = or_slots<W>(got);
-        if (settle<W>(a, alive, v, gl, seen, got & full & ~seen)) {
+        if (settle<W>(a, sums, v, gl, seen, got & full & ~seen)) {
             if (gl == 0) atomicOr(&bits[k >> 5], 1u << (k & 31));
         }
     }
-    alive_out<W>(a, alive);
+    sums_out<W>(a, sums);
     if (tid < kVerts / 32) {
         const int32_t w = base / 32 + tid;
         if (w < (a.n + 31) / 32) {
@@ -267,16 +288,17 @@ __global__ __launch_bounds__(kCloseBlock) void k_close_level(CloseArgs a) {
 }
 
 // Clears the bits of one pass and its levels' search masks (level 0: the
-// count sources of the pass).
+// count sources of the pass) and counters.
 __global__ void k_close_clear(unsigned long long *seen, long long words, uint32_t *act, long long act_words,
-                              unsigned long long *alive, int32_t count) {
+                              unsigned long long *rows, int32_t count) {
     const long long stride = (long long)gridDim.x * blockDim.x;
     const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     for (long long i = t; i < words; i += stride) seen[i] = 0ULL;
     for (long long i = t; i < act_words; i += stride) act[i] = 0u;
-    if (t < 16 * (kCloseDeep + 1)) {
-        const int32_t left = count - 64 * (int32_t)t;
-        alive[t] = t >= 16 || left <= 0 ? 0ULL : left >= 64 ? ~0ULL : (1ULL << left) - 1ULL;
+    for (long long i = t; i < kCloseRows * kCloseRow; i += stride) {
+        const int32_t w = (int32_t)i - kCloseRow;   // (level 0 is row 1)
+        const int32_t left = count - 64 * w;
+        rows[i] = w < 0 || w >= 16 || left <= 0 ? 0ULL : left >= 64 ? ~0ULL : (1ULL << left) - 1ULL;
     }
 }
 
@@ -358,20 +380,51 @@ hipError_t launch_level(int W, const CloseArgs &a, hipStream_t s) {
     }
 }
 
+// The vertices that the searches of a pass found level by level.
+struct CloseGrowth {
+    unsigned long long all, peak, found[4];   // in all; most on two levels; the last four levels, the latest first
+    void add(unsigned long long pairs) {
+        for (int i = 3; i > 0; --i) found[i] = found[i - 1];
+        found[0] = pairs;
+        all += pairs;
+        peak = std::max(peak, pairs + found[1]);
+    }
+    // Whether they will end soon, of the `most` there could be: they have seen
+    // a good part of the graph, or are well past their peak, or still multiply
+    // -- two levels gain over the two before, and at the first look by more
+    // than on a plane, where level l holds some l vertices.  Searches that do
+    // none of these are those of chains, rings and planar lattices.
+    bool ends_soon(bool first, unsigned long long most) const {
+        const double now = (double)(found[0] + found[1]), before = (double)(found[2] + found[3]);
+        const double plane = (2.0 * kCloseFirst - 1.0) / (2.0 * kCloseFirst - 5.0);
+        return all >= most / 8 || 4.0 * now <= (double)peak || now >= (first ? 1.05 * plane : 1.0) * before;
+    }
+};
+
 }  // namespace
 
 nk_status close_bits(const int32_t *rowptr, const int32_t *colidx, int32_t n, int64_t m, const int32_t *sources,
-                     int32_t k, bool sampled, double *out, DevStatus *dst, Scratch &scr, hipStream_t s, bool *done, int *levels) {
+                     int32_t k, bool sampled, double *out, DevStatus *dst, Scratch &scr, hipStream_t s, bool *done,
+                     bool *deep, int *levels) {
     *done = false;
+    *deep = false;
     *levels = 0;
     // A level costs a launch (about 12 us with its latencies, ten levels a
     // pass), the other kernel about k m / 200 G arcs/s and 100 us of
     // preparation: small calls stay there (G(300, 900), 100 sources: 142 us
     // there, 196 here; G(5000, 5000) exact: 1.8 and 3.3 ms; BA-9973, 64
     // sources: 513 and 190 us; exact: 3.7 and 2.2 ms).
+    // A graph of many levels is left after its first look (CloseGrowth), about
+    // 0.1 ms gone; lattices and trees have less than 5 arcs a vertex, and there
+    // the calls that this would lengthen by more than a twelfth stay away (a
+    // 60 x 60 grid, 256 sources: 0.83 ms there, 0.96 with the look; 1024: 1.16
+    // and 1.25; a 300 x 300 grid, 64: 4.3 and 4.3).  Levels run to their end
+    // here against there: 60 x 60 grid, 256 sources 2.3 / 0.8 ms, 20^3 grid
+    // 1.0 / 1.45, small world of 10^5 vertices and 64 sources 0.9 / 6.2.
     if (n > kCloseMax) return NK_OK;
     const bool one_pass = k <= 1024;
-    if (one_pass ? (double)k * (double)m < 2e6 : m < 20000) return NK_OK;
+    const double least = m < 5LL * n && m < 150000 ? 1e7 : 2e6;
+    if (one_pass ? (double)k * (double)m < least : m < 20000) return NK_OK;
     int W = 1;
     while (W < 16 && 64 * W < k) W *= 2;
     // three bit arrays within the scratch allowed (fewer sources a pass
@@ -391,24 +444,30 @@ nk_status close_bits(const int32_t *rowptr, const int32_t *colidx, int32_t n, in
     unsigned long long *seen, *f[2], *acc;
     uint32_t *act;
     int32_t *list0, *list1, *nlist, *reach = nullptr;
-    unsigned long long *alive;
+    unsigned long long *rows;
     // (no more such rows than this)
     const long long max0 = std::min<long long>(n, m / kWaveRow + 1), max1 = std::min<long long>(n, m / kBlockRow + 1);
-    if ((st = scr.get(words, &seen)) != NK_OK) return st;
-    if ((st = scr.get(words, &f[0])) != NK_OK) return st;
-    if ((st = scr.get(words, &f[1])) != NK_OK) return st;
-    if ((st = scr.get(n, &acc)) != NK_OK) return st;
-    if ((st = scr.get(3 * aw, &act)) != NK_OK) return st;
-    if ((st = scr.get(max0, &list0)) != NK_OK) return st;
-    if ((st = scr.get(max1, &list1)) != NK_OK) return st;
-    if ((st = scr.get(2, &nlist)) != NK_OK) return st;
-    if ((st = scr.get(16 * (kCloseDeep + 1), &alive)) != NK_OK) return st;
+    const auto take = [&]() -> nk_status {
+        if ((st = scr.get(words, &seen)) != NK_OK) return st;
+        if ((st = scr.get(words, &f[0])) != NK_OK) return st;
+        if ((st = scr.get(words, &f[1])) != NK_OK) return st;
+        if ((st = scr.get(n, &acc)) != NK_OK) return st;
+        if ((st = scr.get(3 * aw, &act)) != NK_OK) return st;
+        if ((st = scr.get(max0, &list0)) != NK_OK) return st;
+        if ((st = scr.get(max1, &list1)) != NK_OK) return st;
+        if ((st = scr.get(2, &nlist)) != NK_OK) return st;
+        if ((st = scr.get(kCloseRows * kCloseRow, &rows)) != NK_OK) return st;
+        return sampled ? NK_OK : scr.get(n, &reach);
+    };
+    if ((st = take()) != NK_OK) {
+        scr.release_all();
+        if (st != NK_E_NO_MEMORY) return st;
+        clear_error();
+        return NK_OK;
+    }
     NK_HIP(launch_fill_u64(acc, 0ULL, n, s));
     NK_HIP(launch_fill_i32(nlist, 0, 2, s));
-    if (!sampled) {
-        if ((st = scr.get(n, &reach)) != NK_OK) return st;
-        NK_HIP(launch_fill_i32(reach, 0, n, s));
-    }
+    if (!sampled) NK_HIP(launch_fill_i32(reach, 0, n, s));
     hipLaunchKernelGGL(k_close_lists, dim3((n + 255) / 256), dim3(256), 0, s, rowptr, n, list0, list1, nlist, dst);
     NK_HIP(hipGetLastError());
     CloseArgs a;
@@ -418,19 +477,26 @@ nk_status close_bits(const int32_t *rowptr, const int32_t *colidx, int32_t n, in
     a.n = n;
     a.seen = seen;
     a.acc = acc;
-    a.alive = alive;
     a.list[0] = list0;
     a.list[1] = list1;
     a.nlist = nlist;
     a.big_blocks = (int32_t)std::min<long long>(kListBlocks, m / kBlockRow);
     a.wave_blocks = (int32_t)std::min<long long>(kListBlocks, (m / kWaveRow + 3) / 4);
     a.st = dst;
-    int guess = 6;    // levels launched before the searches left are read
+    int guess = kCloseFirst;    // levels launched before the searches left are read
+    // levels the first pass may take: what the other kernel's arcs cost it
+    // (at most 170 arcs/us and source), at 15 us a level
+    const int most_levels = (int)std::max<int64_t>(kCloseDeep, m / (170 * 15));
+    unsigned long long look[kCloseFirst][kCloseRow];
+    // (looks come after kCloseFirst levels and then every fourth, so the rows of
+    // the levels between two looks are neighbours)
+    static_assert((kCloseFirst + 2) % 4 == 0 && kCloseRows % 4 == 0, "rows of a look");
+    const auto row_of = [&](int l) { return rows + (l + 1) % kCloseRows * kCloseRow; };
     for (long long s0 = 0; s0 < k; s0 += 64 * W) {
         const int32_t count = (int32_t)std::min<long long>(64 * W, k - s0);
         const long long grid = std::min<long long>((words + 255) / 256, 16384);
         hipLaunchKernelGGL(k_close_clear, dim3(std::max<long long>(grid, 8)), dim3(256), 0, s, seen, words, act, 3 * aw,
-                           alive, count);
+                           rows, count);
         NK_HIP(hipGetLastError());
         for (int set = 0; set < 2; ++set) {
             hipLaunchKernelGGL(k_close_sources, dim3((count + 255) / 256), dim3(256), 0, s, sources, (int32_t)s0, count, n,
@@ -438,26 +504,46 @@ nk_status close_bits(const int32_t *rowptr, const int32_t *colidx, int32_t n, in
             NK_HIP(hipGetLastError());
         }
         int launched = 0;
+        CloseGrowth growth = {};
+        growth.add((unsigned long long)count);
         for (;;) {
-            const int upto = std::min(launched == 0 ? guess : launched + 4, kCloseDeep);
+            const int from = launched, upto = launched == 0 ? guess : launched + 4;
             while (launched < upto) {
                 const int l = ++launched;
+                unsigned long long *row = row_of(l);
+                if (l + 1 >= kCloseRows) NK_HIP(launch_fill_u64(row, 0ULL, kCloseRow, s));
                 a.level = l;
                 a.front = f[(l - 1) & 1];
                 a.next = f[l & 1];
                 a.act = act + ((l - 1) % 3) * aw;
                 a.act_next = act + (l % 3) * aw;
                 a.act_clear = act + ((l + 1) % 3) * aw;
+                a.alive_prev = row_of(l - 1);
+                a.alive = row;
+                a.counts = row + 16;
                 NK_HIP(launch_level(W, a, s));
             }
-            unsigned long long last[16], any = 0ULL;
-            NK_HIP(hipMemcpyAsync(last, alive + 16 * launched, sizeof(last), hipMemcpyDeviceToHost, s));
+            // the last level's masks; in the first pass every level's counters
+            // too (a later pass goes on to its end, the ones before it are done)
+            unsigned long long any = 0ULL;
+            const int got = s0 == 0 ? launched - from : 1;
+            NK_HIP(hipMemcpyAsync(look, row_of(launched - got + 1), s0 == 0 ? got * sizeof(look[0]) : 16 * sizeof(any),
+                                  hipMemcpyDeviceToHost, s));
             NK_HIP(hipStreamSynchronize(s));
-            for (unsigned long long x : last) any |= x;
+            for (int w = 0; w < 16; ++w) any |= look[got - 1][w];
             if (!any) break;
-            if (launched == kCloseDeep) {
-                // too deep: the caller's other kernel.  The stream is done with
-                // the bits; where they are much of the memory at hand, the pool
+            if (s0 == 0) {
+                for (int i = 0; i < got; ++i) {
+                    unsigned long long pairs = 0;
+                    for (int x = 0; x < kCloseXcd; ++x) pairs += look[i][16 + 16 * x + kCcPairs];
+                    growth.add(pairs);
+                }
+                *deep = launched >= most_levels ||
+                        !growth.ends_soon(from == 0, (unsigned long long)n * (unsigned long long)count);
+            }
+            if (*deep) {
+                // the caller's other kernel.  The stream is done with the
+                // bits; where they are much of the memory at hand, the pool
                 // does not keep them in their sizes either
                 scr.release_all();
                 if (need(W) > avail / 8) pool_trim();

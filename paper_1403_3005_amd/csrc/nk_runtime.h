@@ -200,11 +200,12 @@ nk_status largest_unreached_component(const int32_t *rowptr, const int32_t *coli
 // Closeness by bit-parallel searches, up to 1024 sources a pass
 // (nk_close.hip): exact (sources NULL, k = n) or sampled scores into out.
 // *done = false (nothing written but scratch and, for a source out of
-// range, the status; scr empty again) where the bits do not fit the scratch
-// or the graph has too many levels.  *levels: levels run.
+// range, the status; scr empty again) for small calls, where the bits do not
+// fit the scratch, and where the graph has too many levels (*deep).  *levels:
+// levels run.
 nk_status close_bits(const int32_t *rowptr, const int32_t *colidx, int32_t n, int64_t m, const int32_t *sources,
                      int32_t k, bool sampled, double *out, DevStatus *dst, Scratch &scr, hipStream_t s, bool *done,
-                     int *levels);
+                     bool *deep, int *levels);
 
 // All-in-LDS betweenness plan for graphs needing at most `dyn_bytes` of
 // dynamic LDS; returns false (and plans nothing) when they do not fit or
