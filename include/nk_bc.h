@@ -397,7 +397,7 @@ nk_status nk_batch_plan_finish(nk_batch_plan *plan, void *stream);
 
 /*
  * Statistics of the calling thread's last nk_bc_exact / nk_bc_sources /
- * nk_bc_exact_batched / pair-sampling call (HOST out[32]):
+ * nk_bc_exact_batched / pair-sampling / closeness call (HOST out[32]):
  *   out[0] sources (or samples) processed     out[1] vertices reached
  *   out[2] arcs scanned, forward              out[3] arcs scanned, backward
  *   out[4] shortest-path DAG arcs             out[5] levels run top-down
@@ -412,7 +412,7 @@ nk_status nk_batch_plan_finish(nk_batch_plan *plan, void *stream);
  *           multi-source kernel, 5 a batch split between the all-in-LDS and
  *           multi-source kernels, 6 the group kernel (the workgroups of one
  *           XCD share a source), 7 a batch split between the all-in-LDS and
- *           group kernels
+ *           group kernels, 8 closeness by bit-parallel searches
  *   out[11] arcs of reached vertices (sum of their degrees, over sources)
  *   out[12] dependency-sweep levels run by push
  *   out[13] sources per workgroup task (multi-source kernel; else 1)
@@ -422,6 +422,9 @@ nk_status nk_batch_plan_finish(nk_batch_plan *plan, void *stream);
  *   (pair sampling: out[1] counts the vertices the searches listed; a
  *   search's probed last level is read, and only its meeting vertices,
  *   which the other side listed, are written)
+ *   (closeness by bit-parallel searches: out[2] arcs looked at by all the
+ *   searches of a pass together, out[6] levels of the passes, out[4] and
+ *   out[5] 0)
  *   (nk_bc_weighted: out[2] arcs relaxed in the distance rounds, out[5]
  *   distance rounds, out[6] shortest-path DAG layers, out[4] DAG arcs)
  *   out[16..23] shader-clock cycles per phase, summed over workgroups:

@@ -1524,17 +1524,14 @@ static nk_status closeness_impl(const int32_t *rowptr, const int32_t *colidx, in
         if ((st = thread_events(&ev0, &ev1)) != NK_OK) return st;
         NK_HIP(hipEventRecord(ev0, s));
         bool done = false, deep = false;
-        int levels = 0;
-        if ((st = close_bits(rowptr, colidx, n, m, sources, k, sampled, out, dst, bits, s, &done, &deep, &levels)) !=
-            NK_OK)
+        if ((st = close_bits(rowptr, colidx, n, m, sources, k, sampled, out, dst, bits, s, &done, &deep)) != NK_OK)
             return st;
         NK_HIP(hipEventRecord(ev1, s));
         if (done) {
             st = finish(dst, h, s);
             NK_HIP(hipEventElapsedTime(&ms, ev0, ev1));
             h->stat[kStSources] = (unsigned long long)k;
-            h->stat[kStBu] = (unsigned long long)levels;
-            stats_record(*h, (n + 63) / 64, 256, 0, ms);
+            stats_record(*h, (int)(((long long)n + 63) / 64), 256, 8, ms);
             return st;
         }
         Relabeled g;

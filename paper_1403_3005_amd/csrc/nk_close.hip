@@ -45,8 +45,11 @@ constexpr int kCloseDeep = 96;                   // levels the first pass may ta
 constexpr int kCloseFirst = 6;                   // levels before the first look at them
 constexpr int kCloseRows = 128;                  // levels whose masks and counters are kept
 constexpr int kCloseXcd = 8;                     // counter lines a level
+constexpr int kCloseTotals = 64;                 // lines of the call's totals: eight an XCD, as adds to a line queue up
 constexpr int kCloseRow = 16 * (1 + kCloseXcd);  // words a level: masks, counters
-enum CloseCount { kCcPairs = 0, kCloseCount };   // new (source, vertex) pairs
+// (source, vertex) pairs found, arcs of their vertices, arcs looked at (a
+// level's line holds the first, the call's totals all), levels run
+enum CloseCount { kCcPairs = 0, kCcArcs, kCcScanned, kCcLevels, kCloseCount };
 constexpr int kListBlocks = 2048;                // blocks that take each list, at most
 // A launch holds less than 2^32 threads (a larger one runs nothing and
 // reports nothing), and a level takes four threads a vertex.
@@ -66,7 +69,8 @@ struct CloseArgs {
     unsigned long long *acc;         // distance sums
     const unsigned long long *alive_prev;   // 16 words: the sources that reached something on the last level
     unsigned long long *alive;       // ... on this one (clear)
-    unsigned long long *counts;      // this level's counters, a line per XCD (kCloseCount of them)
+    unsigned long long *counts;      // this level's counter, a line per XCD
+    unsigned long long *totals;      // the call's (kCloseTotals lines)
     const int32_t *list[2];          // rows for a wave, for a block
     const int32_t *nlist;            // their counts
     int32_t level;
@@ -116,10 +120,10 @@ struct CloseSums {
     unsigned long long count[kCloseCount];
 };
 
-// New bits of vertex v (word `word` of them in this lane, slot 0 counts):
-// stored, added to the distance sum; true if there are any.
+// New bits of vertex v of `deg` arcs (word `word` of them in this lane, slot 0
+// counts): stored, added to the distance sum; true if there are any.
 template <int W>
-__device__ __forceinline__ bool settle(const CloseArgs &a, CloseSums<W> &sums, int32_t v, int gl,
+__device__ __forceinline__ bool settle(const CloseArgs &a, CloseSums<W> &sums, int32_t v, int32_t deg, int gl,
                                        unsigned long long seen, unsigned long long fresh) {
     const int word = gl % W;
     const bool mine = gl < W;
@@ -135,23 +139,30 @@ __device__ __forceinline__ bool settle(const CloseArgs &a, CloseSums<W> &sums, i
     if (gl == 0) {
         a.acc[v] += (unsigned long long)a.level * (unsigned long long)c;
         atomicAdd(&sums.count[kCcPairs], (unsigned long long)c);
+        atomicAdd(&sums.count[kCcArcs], (unsigned long long)c * (unsigned long long)deg);
     }
     return true;
 }
 
 // The block's searches that reached something, added to the level's mask
 // (read first: most blocks bring nothing new, and adds to the one line by all
-// XCDs are slow), and its counts, to its XCD's line.
+// XCDs are slow), and its counts, to its XCD's lines.  scanned: arcs this
+// thread looked at.
 template <int W>
-__device__ __forceinline__ void sums_out(const CloseArgs &a, CloseSums<W> &sums) {
+__device__ __forceinline__ void sums_out(const CloseArgs &a, CloseSums<W> &sums, uint32_t scanned) {
+    scanned = wave_sum<uint32_t>(scanned);
+    if (lane_id() == 0 && scanned) atomicAdd(&sums.count[kCcScanned], (unsigned long long)scanned);
     __syncthreads();
     if (threadIdx.x < W) {
         unsigned long long *al = a.alive + threadIdx.x;
         const unsigned long long x = sums.alive[threadIdx.x];
         if (x & ~__hip_atomic_load(al, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicOr(al, x);
-    } else if (threadIdx.x >= kWave && threadIdx.x < kWave + kCloseCount) {
-        const int i = threadIdx.x - kWave;
-        if (sums.count[i]) atomicAdd(a.counts + (xcc_id() & (kCloseXcd - 1)) * 16 + i, sums.count[i]);
+    } else if (threadIdx.x >= kWave && threadIdx.x < kWave + kCcLevels) {
+        const int i = threadIdx.x - kWave, xcd = xcc_id() & (kCloseXcd - 1);
+        if (sums.count[i]) {
+            atomicAdd(a.totals + (xcd * 8 + (blockIdx.x & 7)) * 16 + i, sums.count[i]);
+            if (i == kCcPairs) atomicAdd(a.counts + xcd * 16, sums.count[i]);
+        }
     }
 }
 
@@ -174,6 +185,8 @@ __global__ __launch_bounds__(kCloseBlock) void k_close_level(CloseArgs a) {
     // level (the bits of the others are not looked for)
     const unsigned long long full = a.alive_prev[word];
     int32_t blk = (int32_t)blockIdx.x;
+    uint32_t scanned = 0;
+    if (tid == 0 && blockIdx.x == 0) atomicAdd(a.totals + kCcLevels, 1ULL);
     if (tid < W) sums.alive[tid] = 0ULL;
     if (tid < kCloseCount) sums.count[tid] = 0ULL;
     __syncthreads();
@@ -194,6 +207,7 @@ __global__ __launch_bounds__(kCloseBlock) void k_close_level(CloseArgs a) {
             for (int32_t i = tid; go && i - tid < deg; i += 2 * kCloseBlock) {
                 const int32_t u1 = i + kCloseBlock < deg ? a.ci[a0 + i + kCloseBlock] : -1;
                 const int32_t u2 = i + 2 * kCloseBlock < deg ? a.ci[a0 + i + 2 * kCloseBlock] : -1;
+                scanned += (u >= 0 ? 1u : 0u) + (u1 >= 0 ? 1u : 0u);
                 const unsigned long long c = or_slots<W>(or_heads<W>(a, u) | or_heads<W>(a, u1));
                 if (gl < W && c) atomicOr(&part[word], c);
                 __syncthreads();
@@ -206,13 +220,13 @@ __global__ __launch_bounds__(kCloseBlock) void k_close_level(CloseArgs a) {
             }
             if (tid < kWave) {
                 // the first group settles
-                const bool fresh = settle<W>(a, sums, v, lane < kLanes ? gl : kLanes, seen,
+                const bool fresh = settle<W>(a, sums, v, deg, lane < kLanes ? gl : kLanes, seen,
                                              lane < kLanes ? got & full & ~seen : 0ULL);
                 if (lane == 0 && fresh) atomicOr(&a.act_next[v >> 5], 1u << (v & 31));
             }
             __syncthreads();
         }
-        sums_out<W>(a, sums);
+        sums_out<W>(a, sums, scanned);
         return;
     }
     blk -= a.big_blocks;
@@ -229,6 +243,7 @@ __global__ __launch_bounds__(kCloseBlock) void k_close_level(CloseArgs a) {
             int32_t u = lane < deg ? a.ci[a0 + lane] : -1;
             for (int32_t i = lane; i - lane < deg; i += kWave) {
                 const int32_t u1 = i + kWave < deg ? a.ci[a0 + i + kWave] : -1;
+                scanned += u >= 0 ? 1u : 0u;
                 unsigned long long c = or_slots<W>(or_heads<W>(a, u));
                 c |= __shfl_xor(c, 16, kWave);
                 c |= __shfl_xor(c, 32, kWave);
@@ -236,11 +251,11 @@ __global__ __launch_bounds__(kCloseBlock) void k_close_level(CloseArgs a) {
                 if (__ballot((full & ~(seen | got)) != 0ULL) == 0ULL) break;
                 u = u1;
             }
-            const bool fresh = settle<W>(a, sums, v, lane < kLanes ? gl : kLanes, seen,
+            const bool fresh = settle<W>(a, sums, v, deg, lane < kLanes ? gl : kLanes, seen,
                                          lane < kLanes ? got & full & ~seen : 0ULL);
             if (lane == 0 && fresh) atomicOr(&a.act_next[v >> 5], 1u << (v & 31));
         }
-        sums_out<W>(a, sums);
+        sums_out<W>(a, sums, scanned);
         return;
     }
     blk -= a.wave_blocks;
@@ -267,17 +282,18 @@ __global__ __launch_bounds__(kCloseBlock) void k_close_level(CloseArgs a) {
             const bool go = i - gl < end && !done;
             if (!__any(go)) break;
             const int32_t u1 = go && i + kLanes < end ? a.ci[a0 + i + kLanes] : -1;
-            got |= or_heads<W>(a, go ? u : -1);
+            scanned += u >= 0 ? 1u : 0u;
+            got |= or_heads<W>(a, u);
             const unsigned long long lack = __ballot((full & ~(seen | got)) != 0ULL);
             done = W == kLanes && ((lack >> (lane & ~(kLanes - 1))) & 0xFFFFULL) == 0ULL;
-            u = u1;
+            u = done ? -1 : u1;
         }
         got = or_slots<W>(got);
-        if (settle<W>(a, sums, v, gl, seen, got & full & ~seen)) {
+        if (settle<W>(a, sums, v, deg, gl, seen, got & full & ~seen)) {
             if (gl == 0) atomicOr(&bits[k >> 5], 1u << (k & 31));
         }
     }
-    sums_out<W>(a, sums);
+    sums_out<W>(a, sums, scanned);
     if (tid < kVerts / 32) {
         const int32_t w = base / 32 + tid;
         if (w < (a.n + 31) / 32) {
@@ -303,14 +319,24 @@ __global__ void k_close_clear(unsigned long long *seen, long long words, uint32_
 }
 
 // The sources' own bits: `front` rows of the sources zeroed by the first
-// launch (set = 0), then source i's bit set in both arrays.
-__global__ void k_close_sources(const int32_t *src, int32_t s0, int32_t count, int32_t n, int W,
-                                unsigned long long *seen, unsigned long long *front, uint32_t *act, int32_t set,
-                                DevStatus *st) {
+// launch (set = 0), then source i's bit set in both arrays (and the sources
+// themselves added to the totals).
+__global__ void k_close_sources(const int32_t *rp, const int32_t *src, int32_t s0, int32_t count, int32_t n, int W,
+                                unsigned long long *seen, unsigned long long *front, uint32_t *act,
+                                unsigned long long *totals, int32_t set, DevStatus *st) {
     if (st->err & kErrGraph) return;
     const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int32_t v = i < count ? (src ? src[s0 + i] : s0 + i) : 0;
+    if (set) {
+        const bool ok = i < count && v >= 0 && v < n;
+        const unsigned long long arcs = wave_sum<unsigned long long>(ok ? (unsigned long long)(rp[v + 1] - rp[v]) : 0ULL);
+        const unsigned long long pairs = (unsigned long long)__popcll(__ballot(ok));
+        if (lane_id() == 0) {
+            atomicAdd(totals + kCcPairs, pairs);
+            atomicAdd(totals + kCcArcs, arcs);
+        }
+    }
     if (i >= count) return;
-    const int32_t v = src ? src[s0 + i] : s0 + i;
     if (v < 0 || v >= n) {
         atomicOr(&st->err, kErrArg);
         return;
@@ -354,13 +380,38 @@ __global__ void k_close_reach(const unsigned long long *seen, int W, int32_t n, 
     }
 }
 
+// The call's totals into the status block (by one wave of the last kernel).
+__device__ __forceinline__ void totals_out(const unsigned long long *totals, DevStatus *st) {
+    static_assert(kCloseTotals == kWave, "a line a lane");
+    if (blockIdx.x != 0 || threadIdx.x >= kWave || (st->err & kErrGraph)) return;
+    constexpr int where[kCloseCount] = {kStReached, kStArcsReached, kStArcsFwd, kStBu};
+#pragma unroll
+    for (int i = 0; i < kCloseCount; ++i) {
+        const unsigned long long x = wave_sum<unsigned long long>(totals[16 * threadIdx.x + i]);
+        if (threadIdx.x == 0) st->stat[where[i]] = x;
+    }
+}
+
 // Exact form, generalised to disconnected graphs: reach counts v itself.
-__global__ void k_close_exact(const unsigned long long *acc, const int32_t *reach, int32_t n, double *out) {
+__global__ void k_close_exact(const unsigned long long *acc, const int32_t *reach, int32_t n, double *out,
+                              const unsigned long long *totals, DevStatus *st) {
+    totals_out(totals, st);
     const long long stride = (long long)gridDim.x * blockDim.x;
     for (long long v = (long long)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
         const int32_t r = reach[v];
         const double share = n > 1 ? (double)(r - 1) / (double)(n - 1) : 0.0;
         out[v] = (r <= 1 || n <= 1) ? 0.0 : share * ((double)(r - 1) / (double)(long long)acc[v]);
+    }
+}
+
+// Sampled form (k_close_finish, under the caller's ids).
+__global__ void k_close_sampled(const unsigned long long *acc, int32_t n, int32_t k, double *out,
+                                const unsigned long long *totals, DevStatus *st) {
+    totals_out(totals, st);
+    const long long stride = (long long)gridDim.x * blockDim.x;
+    for (long long v = (long long)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
+        const double F = (double)n / (double)k * (double)acc[v];
+        out[v] = F > 0.0 ? (double)(n - 1) / F : 0.0;
     }
 }
 
@@ -405,10 +456,9 @@ struct CloseGrowth {
 
 nk_status close_bits(const int32_t *rowptr, const int32_t *colidx, int32_t n, int64_t m, const int32_t *sources,
                      int32_t k, bool sampled, double *out, DevStatus *dst, Scratch &scr, hipStream_t s, bool *done,
-                     bool *deep, int *levels) {
+                     bool *deep) {
     *done = false;
     *deep = false;
-    *levels = 0;
     // A level costs a launch (about 12 us with its latencies, ten levels a
     // pass), the other kernel about k m / 200 G arcs/s and 100 us of
     // preparation: small calls stay there (G(300, 900), 100 sources: 142 us
@@ -444,7 +494,7 @@ nk_status close_bits(const int32_t *rowptr, const int32_t *colidx, int32_t n, in
     unsigned long long *seen, *f[2], *acc;
     uint32_t *act;
     int32_t *list0, *list1, *nlist, *reach = nullptr;
-    unsigned long long *rows;
+    unsigned long long *rows, *totals;
     // (no more such rows than this)
     const long long max0 = std::min<long long>(n, m / kWaveRow + 1), max1 = std::min<long long>(n, m / kBlockRow + 1);
     const auto take = [&]() -> nk_status {
@@ -455,8 +505,9 @@ nk_status close_bits(const int32_t *rowptr, const int32_t *colidx, int32_t n, in
         if ((st = scr.get(3 * aw, &act)) != NK_OK) return st;
         if ((st = scr.get(max0, &list0)) != NK_OK) return st;
         if ((st = scr.get(max1, &list1)) != NK_OK) return st;
-        if ((st = scr.get(2, &nlist)) != NK_OK) return st;
         if ((st = scr.get(kCloseRows * kCloseRow, &rows)) != NK_OK) return st;
+        if ((st = scr.get(kCloseTotals * 16 + 1, &totals)) != NK_OK) return st;
+        nlist = reinterpret_cast<int32_t *>(totals + kCloseTotals * 16);
         return sampled ? NK_OK : scr.get(n, &reach);
     };
     if ((st = take()) != NK_OK) {
@@ -466,7 +517,7 @@ nk_status close_bits(const int32_t *rowptr, const int32_t *colidx, int32_t n, in
         return NK_OK;
     }
     NK_HIP(launch_fill_u64(acc, 0ULL, n, s));
-    NK_HIP(launch_fill_i32(nlist, 0, 2, s));
+    NK_HIP(launch_fill_u64(totals, 0ULL, kCloseTotals * 16 + 1, s));
     if (!sampled) NK_HIP(launch_fill_i32(reach, 0, n, s));
     hipLaunchKernelGGL(k_close_lists, dim3((n + 255) / 256), dim3(256), 0, s, rowptr, n, list0, list1, nlist, dst);
     NK_HIP(hipGetLastError());
@@ -477,6 +528,7 @@ nk_status close_bits(const int32_t *rowptr, const int32_t *colidx, int32_t n, in
     a.n = n;
     a.seen = seen;
     a.acc = acc;
+    a.totals = totals;
     a.list[0] = list0;
     a.list[1] = list1;
     a.nlist = nlist;
@@ -499,8 +551,8 @@ nk_status close_bits(const int32_t *rowptr, const int32_t *colidx, int32_t n, in
                            rows, count);
         NK_HIP(hipGetLastError());
         for (int set = 0; set < 2; ++set) {
-            hipLaunchKernelGGL(k_close_sources, dim3((count + 255) / 256), dim3(256), 0, s, sources, (int32_t)s0, count, n,
-                               W, seen, f[0], act, set, dst);
+            hipLaunchKernelGGL(k_close_sources, dim3((count + 255) / 256), dim3(256), 0, s, rowptr, sources, (int32_t)s0,
+                               count, n, W, seen, f[0], act, totals, set, dst);
             NK_HIP(hipGetLastError());
         }
         int launched = 0;
@@ -551,20 +603,18 @@ nk_status close_bits(const int32_t *rowptr, const int32_t *colidx, int32_t n, in
             }
         }
         guess = launched;
-        *levels += launched;
         if (!sampled) {
             hipLaunchKernelGGL(k_close_reach, dim3(std::min<long long>((n + 255LL) / 256, 65536)), dim3(256), 0, s, seen,
                                W, n, reach, dst);
             NK_HIP(hipGetLastError());
         }
     }
-    if (sampled) {
-        NK_HIP(launch_close_finish(acc, nullptr, n, k, out, s));
-    } else {
-        hipLaunchKernelGGL(k_close_exact, dim3(std::min<long long>((n + 255LL) / 256, 65536)), dim3(256), 0, s, acc, reach,
-                           n, out);
-        NK_HIP(hipGetLastError());
-    }
+    const unsigned last = (unsigned)std::min<long long>((n + 255LL) / 256, 65536);
+    if (sampled)
+        hipLaunchKernelGGL(k_close_sampled, dim3(last), dim3(256), 0, s, acc, n, k, out, totals, dst);
+    else
+        hipLaunchKernelGGL(k_close_exact, dim3(last), dim3(256), 0, s, acc, reach, n, out, totals, dst);
+    NK_HIP(hipGetLastError());
     *done = true;
     return NK_OK;
 }

@@ -201,11 +201,11 @@ nk_status largest_unreached_component(const int32_t *rowptr, const int32_t *coli
 // (nk_close.hip): exact (sources NULL, k = n) or sampled scores into out.
 // *done = false (nothing written but scratch and, for a source out of
 // range, the status; scr empty again) for small calls, where the bits do not
-// fit the scratch, and where the graph has too many levels (*deep).  *levels:
-// levels run.
+// fit the scratch, and where the graph has too many levels (*deep).  The
+// counters go to the status.
 nk_status close_bits(const int32_t *rowptr, const int32_t *colidx, int32_t n, int64_t m, const int32_t *sources,
                      int32_t k, bool sampled, double *out, DevStatus *dst, Scratch &scr, hipStream_t s, bool *done,
-                     bool *deep, int *levels);
+                     bool *deep);
 
 // All-in-LDS betweenness plan for graphs needing at most `dyn_bytes` of
 // dynamic LDS; returns false (and plans nothing) when they do not fit or
