@@ -2017,9 +2017,11 @@ __device__ void bidir_sample(const Params &p, Tile<BLOCK> &sm, BiState &bs, cons
 // round trips, so what counts is the samples in flight: four 256-thread
 // workgroups per compute unit (all that their 38 KB of LDS allows) against
 // the two that 170 registers a lane allow (Chung-Lu 10^6, 26,500 samples:
-// kernel 3.94 -> 2.98 ms; three per compute unit 3.20 ms).
+// kernel 3.94 -> 2.98 ms; three per compute unit 3.20 ms).  The other modes
+// come to about 128 registers, the most that four waves a SIMD may have; a few
+// more, and a compute unit holds one 512-thread workgroup instead of two.
 constexpr int min_waves(int block, int mode) {
-    return (mode == kModePair || mode == kModePairHash) && block == 256 ? 4 : 1;
+    return (mode == kModePair || mode == kModePairHash) && block != 256 ? 1 : 4;
 }
 
 template <int BLOCK, bool BMLDS, int MODE>
