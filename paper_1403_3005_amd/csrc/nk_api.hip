@@ -355,7 +355,8 @@ int auto_block(int32_t n_max) {
 // Long thin graphs go the other way, since a level costs its barriers and
 // the sources run side by side (a 6 x 2500 grid, 1024 sources, 98 / 176 /
 // 326 and 27 / 47 / 83): below 6 arcs a vertex -- every planar graph, every
-// tree -- the vertices alone decide.
+// tree -- the vertices alone decide, and a launch that meets a thin graph all
+// the same leaves (Params::narrow).
 static int auto_block_of(int mode, int32_t n, int64_t m, long long ntasks, int cus) {
     const int block = auto_block(n);
     if (block == 1024 || n < 1000 || m < 6LL * n) return block;
@@ -368,17 +369,23 @@ static int auto_block_of(int mode, int32_t n, int64_t m, long long ntasks, int c
 // Words of a per-slot bitmap over m arcs, rounded to 256 bytes.
 static long long dag_words_of(int64_t m) { return ((m + 31) / 32 + 63) / 64 * 64; }
 
-nk_status plan_launch(int mode, int32_t n_max, long long ntasks, int max_slots, LaunchPlan *plan, int64_t m_arcs) {
+nk_status plan_launch(int mode, int32_t n_max, long long ntasks, int max_slots, LaunchPlan *plan, int64_t m_arcs,
+                      bool thin) {
     DevInfo di;
     nk_status st = dev_info(&di);
     if (st != NK_OK) return st;
     nk_tuning t = tuning_get();
     int block = t.block;
+    bool narrow = false;
     if (block != 256 && block != 512 && block != 1024) {
-        block = t.wg_per_cu > 0 ? auto_block(n_max) : auto_block_of(mode, n_max, m_arcs, ntasks, di.cus);
+        block = t.wg_per_cu > 0 || thin ? auto_block(n_max) : auto_block_of(mode, n_max, m_arcs, ntasks, di.cus);
+        narrow = block != auto_block(n_max);
         // a pair sample's search levels are small: more concurrent samples
         // of 256 threads hide more memory latency than fewer wide ones
-        if (mode == kModePair || mode == kModePairHash) block = 256;
+        if (mode == kModePair || mode == kModePairHash) {
+            block = 256;
+            narrow = false;
+        }
     }
     const long long words = ((long long)n_max + 31) / 32;
     const size_t bm_bytes = (size_t)words * 4;
@@ -455,6 +462,7 @@ nk_status plan_launch(int mode, int32_t n_max, long long ntasks, int max_slots, 
     plan->kernel = kr;
     plan->pair_rec = nullptr;
     plan->dag_words = mode == kModeWeighted ? dag_words_of(m_arcs) : 0;
+    plan->narrow = narrow;
     return NK_OK;
 }
 
@@ -699,6 +707,10 @@ static int group_size(const nk_tuning &t, long long nsources, int cus, int per_x
 // offsets, degree sums, candidates.
 static const size_t kGroupCell = 8 + 8 + 6 * 4;
 
+static bool group_by_size(int32_t n_max, int64_t m_arcs) {
+    return n_max >= 100000 && n_max <= 300000 && m_arcs <= 12LL * n_max;
+}
+
 bool group_wanted(int32_t n_max, int64_t m_arcs, long long nsources) {
     const nk_tuning t = tuning_get();
     if ((t.flags & 16) || n_max < 1 || t.batch > 1) return false;
@@ -706,7 +718,7 @@ bool group_wanted(int32_t n_max, int64_t m_arcs, long long nsources) {
     // a source between a few workgroups measured faster than one source per
     // workgroup (mean-degree-8 random and preferential-attachment graphs);
     // flag bit 3 asks for the group kernel on every graph it can take
-    const bool autosel = n_max >= 100000 && n_max <= 300000 && m_arcs <= 12LL * n_max;
+    const bool autosel = group_by_size(n_max, m_arcs);
     DevInfo di;
     if (dev_info(&di) != NK_OK) return false;
     // and so are runs with at most half as many sources as compute units,
@@ -716,9 +728,9 @@ bool group_wanted(int32_t n_max, int64_t m_arcs, long long nsources) {
     // R-MAT 3.6 / 3.0, 5 * 10^5 vertices of mean degree 8 15.5 / 11.6; with 256
     // sources 3.9 / 4.3 and 20.0 / 20.7).  Below 6 arcs a vertex -- every
     // planar graph and tree -- levels can be many and narrow, and each costs
-    // a barrier between workgroups; a dense graph that deep has more than
-    // 2^64 paths, or is a chain of cliques (8,750 cliques of 8, 64 sources:
-    // 141 / 171 ms).
+    // a barrier between workgroups; a dense graph that deep (8,750 cliques of
+    // 8, 64 and 128 sources: 134 / 168 and 136 / 319 ms) ends the launch early
+    // (Params::narrow: 141 and 141).
     const bool few = n_max > kStateMax && m_arcs >= 6LL * n_max && 2 * nsources <= di.cus && !(t.flags & 1) &&
                      t.block == 0 && t.wg_per_cu == 0;
     if (!(t.flags & 8) && !autosel && !few) return false;
@@ -774,6 +786,7 @@ nk_status plan_group(int32_t n_max, long long nsources, GroupPlan *gp) {
     gp->stride = (((long long)n_max + 2) + 63) / 64 * 64;
     gp->timeout = (long long)rate_khz * 1000LL * 20LL;   // 20 s
     gp->reg_wait = gp->timeout;
+    gp->narrow = false;
     gp->lp.mode = kModeBC;
     gp->lp.block = block;
     gp->lp.lds = true;
@@ -815,6 +828,7 @@ nk_status group_alloc(const GroupPlan &gp, Params &p, Scratch &scr) {
     p.xg_nxcc = gp.nxcc;
     p.xg_timeout = gp.timeout;
     p.xg_reg_wait = gp.reg_wait;
+    p.narrow = gp.narrow;
     p.bu_ratio = tuning_get().bu_ratio;
     p.bw_ratio = tuning_get().bw_ratio;
     return NK_OK;
@@ -910,6 +924,7 @@ nk_status persistent_alloc(const LaunchPlan &plan, Params &p, Scratch &scr, hipS
     }
     p.stride = plan.stride;
     p.bm_words = plan.bm_words;
+    p.narrow = plan.narrow;
     // a directed run without in-arcs grows every level top-down
     p.bu_ratio = (p.directed && !p.trowptr) ? 0.0f : tuning_get().bu_ratio;
     p.bw_ratio = tuning_get().bw_ratio;
@@ -1215,11 +1230,15 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
             stats_record(*h, sp.lp.grid, sp.lp.block, 1, ms);
             return st;
         }
+        bool thin = false;
         // plain and linear-scaling sweeps of undirected graphs without edge
         // scores may run one source per XCD group of workgroups
         if (!ebc && !dir && est != kEstBisect && group_wanted(n, m, k)) {
             GroupPlan gp;
+            Scratch own;
             if ((st = plan_group(n, k, &gp)) != NK_OK) return st;
+            // chosen for its few sources: not for thin graphs
+            gp.narrow = !(tuning_get().flags & 8) && !group_by_size(n, m);
             // a second for the device to clear, then the one-source kernel,
             // which needs no company
             gp.reg_wait = (tuning_get().flags & 128) ? -1 : gp.timeout / 20;
@@ -1235,19 +1254,20 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
             p.iso = iso;
             p.st = dst;
             p.linear = est == kEstLinear;
-            if ((st = group_alloc(gp, p, scr)) != NK_OK) return st;
+            if ((st = group_alloc(gp, p, own)) != NK_OK) return st;
             hipEvent_t ev0, ev1;
             if ((st = thread_events(&ev0, &ev1)) != NK_OK) return st;
             if ((st = group_enqueue(gp, p, s, ev0, ev1)) != NK_OK) return st;
             NK_HIP(launch_gather_scores(sa, g.perm, scale, bc, s, dst, h));
             st = finish_written(h, s);
             NK_HIP(hipEventElapsedTime(&ms, ev0, ev1));
-            if (h->err != kErrBusy) {
+            if (h->err != kErrBusy && !(h->err & kErrNarrow)) {
                 stats_record(*h, gp.lp.grid, gp.lp.block, 6, ms);
                 return st;
             }
+            thin = (h->err & kErrNarrow) != 0;
             clear_error();
-            NK_HIP(launch_status_init(dst, s));
+            NK_HIP(launch_run_begin(dst, sa.acc, sa.copies * sa.x, s));
         }
         // or several sources per task
         const int msb = (!ebc && !dir && est != kEstBisect) ? ms_batch_for(n, k) : 1;
@@ -1278,31 +1298,39 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
             stats_set_batch(msb);
             return st;
         }
-        if ((st = plan_launch(est == kEstBisect ? kModeBisect : kModeBC, n, k, 0, &plan, m)) != NK_OK) return st;
-        Params p;
-        memset(&p, 0, sizeof(p));
-        p.rowptr = g.rowptr;
-        p.colidx = g.colidx;
-        p.n = n;
-        p.m = (int32_t)m;
-        p.ntasks = k;
-        p.sources = src;
-        score_params(sa, &p);
-        p.iso = iso;
-        p.st = dst;
-        p.linear = est == kEstLinear;
-        p.ebc = ebc_run;
-        p.directed = dir != nullptr;
-        p.trowptr = dir ? dir->trp : nullptr;
-        p.tcolidx = dir ? dir->tci : nullptr;
-        hipEvent_t ev0, ev1;
-        if ((st = thread_events(&ev0, &ev1)) != NK_OK) return st;
-        if ((st = launch_persistent(plan, p, scr, s, ev0, ev1)) != NK_OK) return st;
-        NK_HIP(launch_gather_scores(sa, g.perm, scale, bc, s));
-        if (ebc && g.perm) NK_HIP(launch_arcs_back(ebc_run, g.rowptr, g.inv, rowptr, n, ebc, s));
-        if (ebc) NK_HIP(launch_edge_symmetrize(rowptr, colidx, n, ebc, scale, dst, s));
-        st = finish(dst, h, s);
-        NK_HIP(hipEventElapsedTime(&ms, ev0, ev1));
+        for (;; thin = true) {
+            if ((st = plan_launch(est == kEstBisect ? kModeBisect : kModeBC, n, k, 0, &plan, m, thin)) != NK_OK)
+                return st;
+            Scratch own;
+            Params p;
+            memset(&p, 0, sizeof(p));
+            p.rowptr = g.rowptr;
+            p.colidx = g.colidx;
+            p.n = n;
+            p.m = (int32_t)m;
+            p.ntasks = k;
+            p.sources = src;
+            score_params(sa, &p);
+            p.iso = iso;
+            p.st = dst;
+            p.linear = est == kEstLinear;
+            p.ebc = ebc_run;
+            p.directed = dir != nullptr;
+            p.trowptr = dir ? dir->trp : nullptr;
+            p.tcolidx = dir ? dir->tci : nullptr;
+            hipEvent_t ev0, ev1;
+            if ((st = thread_events(&ev0, &ev1)) != NK_OK) return st;
+            if ((st = launch_persistent(plan, p, own, s, ev0, ev1)) != NK_OK) return st;
+            NK_HIP(launch_gather_scores(sa, g.perm, scale, bc, s));
+            if (ebc && g.perm) NK_HIP(launch_arcs_back(ebc_run, g.rowptr, g.inv, rowptr, n, ebc, s));
+            if (ebc) NK_HIP(launch_edge_symmetrize(rowptr, colidx, n, ebc, scale, dst, s));
+            st = finish(dst, h, s);
+            NK_HIP(hipEventElapsedTime(&ms, ev0, ev1));
+            if (!(h->err & kErrNarrow)) break;
+            clear_error();
+            NK_HIP(launch_run_begin(dst, sa.acc, sa.copies * sa.x, s));
+            if (ebc_run) NK_HIP(launch_fill_f64(ebc_run, 0.0, m, s));
+        }
     } else {
         st = finish(dst, h, s);
     }
@@ -1404,25 +1432,31 @@ nk_status nk_bc_weighted(const int32_t *rowptr, const int32_t *colidx, const int
                 src = mapped;
             }
         }
-        if ((st = plan_launch(kModeWeighted, n, k, 0, &plan, m)) != NK_OK) return st;
-        Params p;
-        memset(&p, 0, sizeof(p));
-        p.rowptr = g.rowptr;
-        p.colidx = g.colidx;
-        p.n = n;
-        p.m = (int32_t)m;
-        p.ntasks = k;
-        p.sources = src;
-        score_params(sa, &p);
-        p.st = dst;
-        p.wts = wts;
-        p.wdelta = wdelta;
-        hipEvent_t ev0, ev1;
-        if ((st = thread_events(&ev0, &ev1)) != NK_OK) return st;
-        if ((st = launch_persistent(plan, p, scr, s, ev0, ev1)) != NK_OK) return st;
-        NK_HIP(launch_gather_scores(sa, g.perm, scale, bc, s));
-        st = finish(dst, h, s);
-        NK_HIP(hipEventElapsedTime(&ms, ev0, ev1));
+        for (bool thin = false;; thin = true) {
+            if ((st = plan_launch(kModeWeighted, n, k, 0, &plan, m, thin)) != NK_OK) return st;
+            Scratch own;
+            Params p;
+            memset(&p, 0, sizeof(p));
+            p.rowptr = g.rowptr;
+            p.colidx = g.colidx;
+            p.n = n;
+            p.m = (int32_t)m;
+            p.ntasks = k;
+            p.sources = src;
+            score_params(sa, &p);
+            p.st = dst;
+            p.wts = wts;
+            p.wdelta = wdelta;
+            hipEvent_t ev0, ev1;
+            if ((st = thread_events(&ev0, &ev1)) != NK_OK) return st;
+            if ((st = launch_persistent(plan, p, own, s, ev0, ev1)) != NK_OK) return st;
+            NK_HIP(launch_gather_scores(sa, g.perm, scale, bc, s));
+            st = finish(dst, h, s);
+            NK_HIP(hipEventElapsedTime(&ms, ev0, ev1));
+            if (!(h->err & kErrNarrow)) break;
+            clear_error();
+            NK_HIP(launch_run_begin(dst, sa.acc, sa.copies * sa.x, s));
+        }
     } else {
         st = finish(dst, h, s);
     }
@@ -1548,25 +1582,32 @@ static nk_status closeness_impl(const int32_t *rowptr, const int32_t *colidx, in
             if ((st = scr.get(n, &acc)) != NK_OK) return st;
             NK_HIP(launch_fill_u64(acc, 0ULL, n, s));
         }
-        // (a deep graph is a thin one more often than not: narrow workgroups)
-        if ((st = plan_launch(kModeClose, n, k, 0, &plan, deep ? 0 : m)) != NK_OK) return st;
-        Params p;
-        memset(&p, 0, sizeof(p));
-        p.rowptr = g.rowptr;
-        p.colidx = g.colidx;
-        p.n = n;
-        p.m = (int32_t)m;
-        p.ntasks = k;
-        p.sources = src;
-        p.inv = g.inv;
-        p.iso = iso;
-        p.st = dst;
-        p.close_out = sampled ? nullptr : out;
-        p.close_acc = acc;
-        if ((st = launch_persistent(plan, p, scr, s, ev0, ev1)) != NK_OK) return st;
-        if (sampled) NK_HIP(launch_close_finish(acc, g.perm, n, k, out, s));
-        st = finish(dst, h, s);
-        NK_HIP(hipEventElapsedTime(&ms, ev0, ev1));
+        // (a graph too deep for the bits is a thin one more often than not)
+        for (bool thin = deep;; thin = true) {
+            if ((st = plan_launch(kModeClose, n, k, 0, &plan, m, thin)) != NK_OK) return st;
+            Scratch own;
+            Params p;
+            memset(&p, 0, sizeof(p));
+            p.rowptr = g.rowptr;
+            p.colidx = g.colidx;
+            p.n = n;
+            p.m = (int32_t)m;
+            p.ntasks = k;
+            p.sources = src;
+            p.inv = g.inv;
+            p.iso = iso;
+            p.st = dst;
+            p.close_out = sampled ? nullptr : out;
+            p.close_acc = acc;
+            if ((st = launch_persistent(plan, p, own, s, ev0, ev1)) != NK_OK) return st;
+            if (sampled) NK_HIP(launch_close_finish(acc, g.perm, n, k, out, s));
+            st = finish(dst, h, s);
+            NK_HIP(hipEventElapsedTime(&ms, ev0, ev1));
+            if (!(h->err & kErrNarrow)) break;
+            clear_error();
+            NK_HIP(launch_status_init(dst, s));
+            if (sampled) NK_HIP(launch_fill_u64(acc, 0ULL, n, s));
+        }
     } else {
         st = finish(dst, h, s);
     }
@@ -1624,22 +1665,28 @@ nk_status nk_sssp_counts(const int32_t *rowptr, const int32_t *colidx, int32_t n
     NK_HIP(launch_fill_i32(d, -1, (long long)k * n, s));
     NK_HIP(launch_fill_u64((unsigned long long *)sigma, 0ULL, (long long)k * n, s));
     LaunchPlan plan;
-    if ((st = plan_launch(kModeSSSP, n, k, 0, &plan, m)) != NK_OK) return st;
-    Params p;
-    memset(&p, 0, sizeof(p));
-    p.rowptr = g.rowptr;
-    p.colidx = g.colidx;
-    p.n = n;
-    p.m = (int32_t)m;
-    p.ntasks = k;
-    p.sources = src;
-    p.d_out = d;
-    p.sigma_out = (unsigned long long *)sigma;
-    p.inv = g.inv;
-    p.iso = iso;
-    p.st = dst;
-    if ((st = launch_persistent(plan, p, scr, s, nullptr, nullptr)) != NK_OK) return st;
-    st = finish(dst, h, s);
+    for (bool thin = false;; thin = true) {
+        if ((st = plan_launch(kModeSSSP, n, k, 0, &plan, m, thin)) != NK_OK) return st;
+        Scratch own;
+        Params p;
+        memset(&p, 0, sizeof(p));
+        p.rowptr = g.rowptr;
+        p.colidx = g.colidx;
+        p.n = n;
+        p.m = (int32_t)m;
+        p.ntasks = k;
+        p.sources = src;
+        p.d_out = d;
+        p.sigma_out = (unsigned long long *)sigma;
+        p.inv = g.inv;
+        p.iso = iso;
+        p.st = dst;
+        if ((st = launch_persistent(plan, p, own, s, nullptr, nullptr)) != NK_OK) return st;
+        st = finish(dst, h, s);
+        if (!(h->err & kErrNarrow)) break;
+        clear_error();
+        NK_HIP(launch_status_init(dst, s));
+    }
     stats_record(*h, plan.grid, plan.block, plan.lds, 0.0f);
     return st;
 }

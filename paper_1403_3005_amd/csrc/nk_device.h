@@ -20,7 +20,8 @@ enum : int32_t {
     kErrArg = 2,        // a source id or pair index out of range
     kErrOverflow = 4,   // a path count wrapped past 2^64 - 1
     kErrInternal = 8,   // list capacity exceeded (only after a wrap)
-    kErrBusy = 16       // a group launch's workgroups were not all resident in time: nothing was run
+    kErrBusy = 16,      // a group launch's workgroups were not all resident in time: nothing was run
+    kErrNarrow = 32     // a launch planned for wide levels met a thin graph and left: nothing counts
 };
 
 // Per-call device status block: error bits, the dynamic task counter and

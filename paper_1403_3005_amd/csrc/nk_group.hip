@@ -338,7 +338,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 1) void k_brandes_group(P
         // the leader takes the next task and broadcasts it; the reset of the
         // previous task is complete (barrier at the end of the loop)
         if (lead && tid == 0) {
-            const long long t = (long long)atomicAdd(&p.st->head, 1ULL);
+            const long long t = left_thin(p) ? p.ntasks : (long long)atomicAdd(&p.st->head, 1ULL);
             ctl->task[it & 1].v = (unsigned long long)t;
         }
         if (!group_sync(gs, ctl, p)) break;
@@ -564,6 +564,12 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 1) void k_brandes_group(P
             f0 = f1;
             f1 = f1 + nnew;
             ++d;
+            if (found_thin(p, kThin, d, f1)) {
+                // (every member sees the same counts and leaves here)
+                if (lead && tid == 0) atomicOr(&p.st->err, kErrNarrow);
+                ok = false;
+                break;
+            }
         }
         if (!ok) break;
         const int32_t Ld = d;            // deepest non-empty level: list [f0, f1)

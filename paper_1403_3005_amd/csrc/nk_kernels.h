@@ -60,7 +60,7 @@ struct Params {
     double *bc;                // scores: copy x (of bc_mask + 1) starts at bc + x * bc_x
     long long bc_x;
     int32_t bc_mask;
-    int32_t pad5;
+    int32_t narrow;            // != 0: leave (kErrNarrow) on a thin graph, see found_thin
     int32_t *d_out;
     unsigned long long *sigma_out;
     uint32_t *counts;
@@ -167,6 +167,27 @@ struct Params {
     long long *defer;
     unsigned long long *defer_count;
 };
+
+// Wide workgroups, and several of them a source, pay on graphs whose levels are
+// wide; on chains and rings, whose levels are a few vertices each, a level
+// costs its barriers, and fewer sources run side by side (1,500 cliques of 16
+// in a chain, 1024 sources' edge scores: 53 ms with 512 threads, 94 with 1024;
+// a chain of 8,750 cliques of 8, 128 sources: 136 ms with a workgroup a source,
+// 319 with four).  Depth is known only once a search runs, so a launch whose
+// plan was chosen for wide levels leaves when a search has found less than 1024
+// vertices in 32 levels, or a weighted one, whose rounds are smaller than
+// levels, 256 in 32 rounds or 2048 in 128 (a small world of 2 * 10^4 vertices
+// has some hundreds after 32 and then multiplies), and the call starts over on
+// the other plan: 0.2 to 1.5 ms late, of runs that take several times as long.
+struct ThinLine { int32_t levels, found; };
+constexpr ThinLine kThin = {32, 1024}, kThinW[2] = {{32, 256}, {128, 2048}};
+__device__ __forceinline__ bool found_thin(const Params &p, ThinLine t, int32_t levels, int32_t found) {
+    return p.narrow != 0 && levels == t.levels && found < t.found;
+}
+// Whether a workgroup has left that way (the others take no further task).
+__device__ __forceinline__ bool left_thin(const Params &p) {
+    return p.narrow != 0 && (__hip_atomic_load(&p.st->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kErrNarrow);
+}
 
 // The copy of the scores this workgroup adds into.  Every source adds to
 // every reached vertex, and an add from another XCD moves the line from

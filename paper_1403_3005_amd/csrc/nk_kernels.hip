@@ -412,8 +412,8 @@ __device__ void bu_level(const Params &p, Tile<BLOCK> &sm, uint32_t *bm, const S
     if (ovf) atomicOr(&p.st->err, kErrOverflow);
 }
 
-// Forward phase from `src`.  Returns the deepest non-empty level Ld; the
-// list holds levels 0..Ld at s.lvl[l] .. s.lvl[l+1].
+// Forward phase from `src`.  Returns the deepest non-empty level Ld (-1: the
+// launch is to be left); the list holds levels 0..Ld at s.lvl[l] .. s.lvl[l+1].
 template <int BLOCK, int MODE>
 __device__ int32_t forward(const Params &p, Tile<BLOCK> &sm, uint32_t *bm, const Scr &s, const GView &g,
                            const uint32_t *iso, int32_t src, Counters &c) {
@@ -500,6 +500,7 @@ __device__ int32_t forward(const Params &p, Tile<BLOCK> &sm, uint32_t *bm, const
         phase_end<BLOCK>(sm, kPhMark);
         if (nnew == 0) break;
         ++lvl;
+        if (found_thin(p, kThin, lvl, f1 + nnew)) return -1;
     }
     return lvl;
 }
@@ -918,7 +919,7 @@ __device__ int32_t w_distances(const Params &p, Tile<BLOCK> &sm, uint32_t *bm, c
         s_far = 0;
     }
     __syncthreads();
-    int32_t cur = 0, ncur = 1;
+    int32_t cur = 0, ncur = 1, rounds = 0;
     long long npend = 0;   // pending list length (uniform across the workgroup)
     for (;;) {
         ++ep;
@@ -1050,6 +1051,9 @@ __device__ int32_t w_distances(const Params &p, Tile<BLOCK> &sm, uint32_t *bm, c
         if (nn == 0) break;
         cur ^= 1;
         ncur = nn;
+        // (s_reach grows again only past the next round's barriers)
+        ++rounds;
+        if (found_thin(p, kThinW[0], rounds, s_reach) || found_thin(p, kThinW[1], rounds, s_reach)) return -1;
     }
     return s_reach;
 }
@@ -2084,7 +2088,7 @@ __global__ __launch_bounds__(BLOCK, min_waves(BLOCK, MODE)) void k_brandes(Param
     (void)ep;
     (void)pfilt;
     for (;;) {
-        if (tid == 0) sm.task = (long long)atomicAdd(&p.st->head, 1ULL);
+        if (tid == 0) sm.task = !PAIR && left_thin(p) ? p.ntasks : (long long)atomicAdd(&p.st->head, 1ULL);
         __syncthreads();
         const long long task = sm.task;
         __syncthreads();
@@ -2179,6 +2183,10 @@ __global__ __launch_bounds__(BLOCK, min_waves(BLOCK, MODE)) void k_brandes(Param
             phase_start<BLOCK>(sm);
             const int32_t nreach = w_distances<BLOCK>(p, sm, bm, s, g, src, ep, c);
             phase_end<BLOCK>(sm, kPhTd);
+            if (nreach < 0) {
+                if (tid == 0) atomicOr(&p.st->err, kErrNarrow);
+                break;
+            }
             phase_start<BLOCK>(sm);
             // the distance-bucket histogram sits at the start of the dynamic
             // LDS (the settled bitmap's place when that is in LDS; it is not
@@ -2213,6 +2221,10 @@ __global__ __launch_bounds__(BLOCK, min_waves(BLOCK, MODE)) void k_brandes(Param
         } else {
 
         const int32_t Ld = forward<BLOCK, MODE>(p, sm, bm, s, g, p.G > 0 ? nullptr : p.iso, src, c);
+        if (Ld < 0) {
+            if (tid == 0) atomicOr(&p.st->err, kErrNarrow);
+            break;
+        }
         const int32_t nreached = s.lvl[Ld + 1];
         if (tid == 0) {
             c.reached += (unsigned long long)nreached;

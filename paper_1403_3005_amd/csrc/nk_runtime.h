@@ -111,6 +111,7 @@ struct LaunchPlan {
     KernelRef kernel;
     void *pair_rec;   // pair mode: the record block the launch used (set by the caller after the launch)
     long long dag_words;   // weighted mode: per-slot words of the DAG-arc bitmap
+    bool narrow;           // a thin graph ends the launch (Params::narrow): plan again with thin = true
 };
 // The tag a pair-mode record block of `plan` carries after a successful
 // launch (records or hash tables, by the plan's mode).
@@ -121,9 +122,10 @@ inline uint64_t pair_block_tag(const LaunchPlan &plan) {
 // Picks block size, bitmap placement and grid for graphs of at most n_max
 // vertices and `ntasks` tasks.  max_slots > 0 caps the grid.  m_arcs: the
 // arcs of the graph (weighted mode sizes its DAG-arc bitmap by them; 0 = not
-// known, and the block size then goes by the vertices alone).
+// known).  The block size goes by the vertices alone where m_arcs is 0 or thin
+// is set (a graph of many narrow levels).
 nk_status plan_launch(int mode, int32_t n_max, long long ntasks, int max_slots, LaunchPlan *plan,
-                      int64_t m_arcs = 0);
+                      int64_t m_arcs = 0, bool thin = false);
 // Block size of a persistent launch over graphs of at most n_max vertices
 // when the tuning leaves it open.
 int auto_block(int32_t n_max);
@@ -160,6 +162,7 @@ struct GroupPlan {
     long long stride;      // per-group vertex capacity
     long long timeout;     // wall-clock ticks a wait may last
     long long reg_wait;    // ... and the wait for the whole grid to be resident
+    bool narrow;           // a thin graph ends the launch (Params::narrow)
 };
 // Whether the group kernel takes a graph of n_max vertices and m_arcs arcs:
 // automatically for sparse graphs of 10^5 to 3 * 10^5 vertices, for every
