@@ -1240,8 +1240,9 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
             // chosen for its few sources: not for thin graphs
             gp.narrow = !(tuning_get().flags & 8) && !group_by_size(n, m);
             // a second for the device to clear, then the one-source kernel,
-            // which needs no company
-            gp.reg_wait = (tuning_get().flags & 128) ? -1 : gp.timeout / 20;
+            // which needs no company; 10 ms for few sources, a few times what
+            // they take there
+            gp.reg_wait = (tuning_get().flags & 128) ? -1 : gp.timeout / (gp.narrow ? 2000 : 20);
             Params p;
             memset(&p, 0, sizeof(p));
             p.rowptr = g.rowptr;
