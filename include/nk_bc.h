@@ -552,7 +552,9 @@ nk_status nk_tuning_lookup(const char *cache_path, int32_t n, int64_t m, int64_t
  * batch and, for eight-value entries, group and flag bits 3 and 4 (the
  * other flags and scratch_mib stay those of nk_set_tuning), found by one
  * maximum-degree reduction per call; other graphs run under the global
- * tuning.  The file is read when registered and re-read when nk_autotune
+ * tuning.  An entry holds for many sources: a plain or linear-scaling call
+ * that the automatic choice gives to the group kernel for its few sources
+ * (flags bit 4) takes the ratios alone from it.  The file is read when registered and re-read when nk_autotune
  * writes it.  NK_E_INVALID_ARG if it cannot be read.
  */
 nk_status nk_set_tuning_cache(const char *cache_path);

@@ -707,6 +707,20 @@ static int group_size(const nk_tuning &t, long long nsources, int cus, int per_x
 // offsets, degree sums, candidates.
 static const size_t kGroupCell = 8 + 8 + 6 * 4;
 
+// Runs with at most half as many sources as compute units, which leave most of
+// the device idle at one source per workgroup, past the state-in-LDS kernel's
+// graphs, if launch shape and placement are left to the library (ms one-source
+// / group: 128 sources, 131,072-vertex R-MAT 3.6 / 3.0, 5 * 10^5 vertices of
+// mean degree 8 15.5 / 11.6; with 256 sources 3.9 / 4.3 and 20.0 / 20.7).  Below 6
+// arcs a vertex -- every planar graph and tree -- levels can be many and
+// narrow, and each costs a barrier between workgroups; a dense graph that deep
+// (8,750 cliques of 8, 64 and 128 sources: 134 / 168 and 136 / 319 ms) ends the
+// launch early (Params::narrow: 141 and 141).
+static bool group_by_sources(const nk_tuning &t, int32_t n_max, int64_t m_arcs, long long nsources, int cus) {
+    return n_max > kStateMax && m_arcs >= 6LL * n_max && 2 * nsources <= cus && !(t.flags & (1 | 16)) && t.block == 0 &&
+           t.wg_per_cu == 0 && t.batch <= 1;
+}
+
 static bool group_by_size(int32_t n_max, int64_t m_arcs) {
     return n_max >= 100000 && n_max <= 300000 && m_arcs <= 12LL * n_max;
 }
@@ -721,18 +735,8 @@ bool group_wanted(int32_t n_max, int64_t m_arcs, long long nsources) {
     const bool autosel = group_by_size(n_max, m_arcs);
     DevInfo di;
     if (dev_info(&di) != NK_OK) return false;
-    // and so are runs with at most half as many sources as compute units,
-    // which leave most of the device idle at one source per workgroup, past
-    // the state-in-LDS kernel's graphs, if launch shape and placement are
-    // left to the library (ms one-source / group: 128 sources, 131,072-vertex
-    // R-MAT 3.6 / 3.0, 5 * 10^5 vertices of mean degree 8 15.5 / 11.6; with 256
-    // sources 3.9 / 4.3 and 20.0 / 20.7).  Below 6 arcs a vertex -- every
-    // planar graph and tree -- levels can be many and narrow, and each costs
-    // a barrier between workgroups; a dense graph that deep (8,750 cliques of
-    // 8, 64 and 128 sources: 134 / 168 and 136 / 319 ms) ends the launch early
-    // (Params::narrow: 141 and 141).
-    const bool few = n_max > kStateMax && m_arcs >= 6LL * n_max && 2 * nsources <= di.cus && !(t.flags & 1) &&
-                     t.block == 0 && t.wg_per_cu == 0;
+    // and so are runs of few sources
+    const bool few = group_by_sources(t, n_max, m_arcs, nsources, di.cus);
     if (!(t.flags & 8) && !autosel && !few) return false;
     if (!(t.flags & 8) && !autosel) {
         // its scratch, under the limit a one-source launch is cut to
@@ -1119,6 +1123,20 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
         int64_t dmax = 0;
         if ((st = graph_max_degree(rowptr, n, s, &dmax)) != NK_OK) return st;
         use_cached = cached_tuning(n, m, dmax, &cached);
+        // Entries know shapes, not numbers of sources: few sources go to the
+        // kernel for them, with the entry's ratios (131,072-vertex R-MAT, 64
+        // sources, an entry of the one-source kernel: 2.3 ms under it, 1.2).
+        DevInfo di;
+        if ((st = dev_info(&di)) != NK_OK) return st;
+        const nk_tuning base = tuning_get();
+        if (use_cached && !ebc && !dir && est != kEstBisect && !(base.flags & 8) &&
+            group_by_sources(base, n, m, k, di.cus)) {
+            cached.block = base.block;
+            cached.wg_per_cu = base.wg_per_cu;
+            cached.flags = base.flags;
+            cached.batch = base.batch;
+            cached.group = base.group;
+        }
     }
     TuningOverride cached_scope(use_cached ? &cached : nullptr);
     Scratch scr;
