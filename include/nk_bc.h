@@ -519,7 +519,9 @@ nk_status nk_get_tuning(nk_tuning *t);
 /*
  * Autotuner: times with nk_bc_sources on the given sample of sources
  * (DEVICE int32[k]) every setting of block in {256, 512, 1024}, bu_ratio in
- * {0, 2, 8, 16, 64} and bw_ratio in {0, 0.1, 0.25, 1} (one source per task),
+ * {0, 2, 8, 16, 64} and bw_ratio in {0, 0.1, 0.25, 1} (one source per task;
+ * the ratios only where the kernel that takes the graph looks at them: not
+ * bw_ratio with the source's state in LDS, neither with the graph there),
  * on the one-source kernel (flags bit 4), then from the fastest of those
  * one resident workgroup per compute unit, batch = 4, 8 and 16 sources per
  * task (block 1024) and, where its bitmap fits LDS, the group kernel
@@ -531,7 +533,7 @@ nk_status nk_get_tuning(nk_tuning *t);
  * degree / mean degree) in a flat JSON object
  * {"bucket": [block, bu_ratio, bw_ratio, wg_per_cu, batch, ms,
  * kernel_flags, group]}, kernel_flags being the winner's flag bits 3 and 4
- * (8 or 16).  Entries of six values (no kernel choice) and of four
+ * (8 or 16), plus 256 where the graph's state fits LDS.  Entries of six values (no kernel choice) and of four
  * ([block, bu_ratio, bw_ratio, ms]) are read as well.
  */
 nk_status nk_autotune(const int32_t *rowptr, const int32_t *colidx, int32_t n, int64_t m, const int32_t *sources,
@@ -554,7 +556,11 @@ nk_status nk_tuning_lookup(const char *cache_path, int32_t n, int64_t m, int64_t
  * maximum-degree reduction per call; other graphs run under the global
  * tuning.  An entry holds for many sources: a plain or linear-scaling call
  * that the automatic choice gives to the group kernel for its few sources
- * (flags bit 4) takes the ratios alone from it.  The file is read when registered and re-read when nk_autotune
+ * (flags bit 4) takes the ratios alone from it.  An entry made where the
+ * graph's state fits LDS (kernel_flags bit 8) does not apply to the other
+ * calls, bisection, edge, directed and server, which run elsewhere; one made
+ * elsewhere gives plain calls that run there neither block nor bu_ratio.  The
+ * file is read when registered and re-read when nk_autotune
  * writes it.  NK_E_INVALID_ARG if it cannot be read.
  */
 nk_status nk_set_tuning_cache(const char *cache_path);

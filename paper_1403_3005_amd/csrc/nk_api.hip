@@ -562,6 +562,20 @@ bool plan_state(int32_t n_max, long long ntasks, StatePlan *sp) {
     return true;
 }
 
+// Where graphs of n vertices and m arcs run with their state in LDS under the
+// tuning *t but for its block and bu_ratio, those of the caller's tuning take
+// their place: *t was timed on another kernel.
+static void state_tuning(int32_t n, int64_t m, long long ntasks, nk_tuning *t) {
+    const nk_tuning base = tuning_get();
+    nk_tuning own = *t;
+    own.block = base.block;
+    own.bu_ratio = base.bu_ratio;
+    TuningOverride scope(&own);
+    LaunchPlan lp;
+    StatePlan sp;
+    if (!plan_lds(lds_graph_bytes(n, m), n, ntasks, &lp) && plan_state(n, ntasks, &sp)) *t = own;
+}
+
 nk_status state_alloc(const StatePlan &sp, Params &p, Scratch &scr) {
     nk_status st;
     p.sigma = nullptr;
@@ -1122,14 +1136,20 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
     if (tuning_cache_active()) {
         int64_t dmax = 0;
         if ((st = graph_max_degree(rowptr, n, s, &dmax)) != NK_OK) return st;
-        use_cached = cached_tuning(n, m, dmax, &cached);
+        bool in_lds = false;
+        use_cached = cached_tuning(n, m, dmax, &cached, &in_lds);
+        const bool plain = !ebc && !dir && est != kEstBisect;
+        // an entry timed on the kernels with the state in LDS is for calls
+        // that run there, and one timed on the others for calls that do not
+        if (in_lds && !plain) use_cached = false;
+        if (use_cached && !in_lds && plain) state_tuning(n, m, k, &cached);
         // Entries know shapes, not numbers of sources: few sources go to the
         // kernel for them, with the entry's ratios (131,072-vertex R-MAT, 64
         // sources, an entry of the one-source kernel: 2.3 ms under it, 1.2).
         DevInfo di;
         if ((st = dev_info(&di)) != NK_OK) return st;
         const nk_tuning base = tuning_get();
-        if (use_cached && !ebc && !dir && est != kEstBisect && !(base.flags & 8) &&
+        if (use_cached && plain && !(base.flags & 8) &&
             group_by_sources(base, n, m, k, di.cus)) {
             cached.block = base.block;
             cached.wg_per_cu = base.wg_per_cu;
@@ -2068,8 +2088,8 @@ static nk_status batch_prepare(int32_t G, const int64_t *vtx_off, const int64_t 
     }
     // the large graphs' launch runs under the registered autotuner cache's
     // tuning for the largest of them, if it has one
-    nk_tuning cached;
-    bool use_cached = false;
+    nk_tuning cached, state_cached;
+    bool use_cached = false, in_lds = false;
     if (!large.empty() && tuning_cache_active()) {
         int32_t gbig = large[0];
         for (int32_t g : large)
@@ -2077,10 +2097,19 @@ static nk_status batch_prepare(int32_t G, const int64_t *vtx_off, const int64_t 
         int64_t dmax = 0;
         const int32_t nb = (int32_t)(vtx_off[gbig + 1] - vtx_off[gbig]);
         if ((st = graph_max_degree(rowptr_cat + vtx_off[gbig] + gbig, nb, s, &dmax)) != NK_OK) return st;
-        use_cached = cached_tuning(nb, arc_off[gbig + 1] - arc_off[gbig], dmax, &cached);
+        use_cached = cached_tuning(nb, arc_off[gbig + 1] - arc_off[gbig], dmax, &cached, &in_lds);
+    }
+    if (use_cached) {
+        // (an entry timed on another kernel: as state_tuning)
+        state_cached = cached;
+        if (!in_lds) {
+            state_cached.block = tuning_get().block;
+            state_cached.bu_ratio = tuning_get().bu_ratio;
+        }
     }
     TuningOverride cached_scope(use_cached ? &cached : nullptr);
     {
+        TuningOverride state_scope(use_cached ? &state_cached : nullptr);
         // those whose per-source state fits LDS leave for its kernel
         std::vector<int32_t> rest;
         b->n_large = 0;

@@ -88,8 +88,9 @@ private:
 // Autotuner cache (nk_tune.hip): the tuning registered for graphs shaped
 // like (n, m, max degree), merged into the global tuning (flags and
 // scratch cap stay global); false when no cache is registered or it has no
-// entry for the shape.
-bool cached_tuning(int32_t n, int64_t m, int64_t max_deg, nk_tuning *out);
+// entry for the shape.  *in_lds: the entry was timed on a kernel of
+// nk_lds.hip, and its block and ratios say nothing of the others.
+bool cached_tuning(int32_t n, int64_t m, int64_t max_deg, nk_tuning *out, bool *in_lds);
 bool tuning_cache_active();
 // Maximum degree of a CSR (one reduction kernel; synchronises s).
 nk_status graph_max_degree(const int32_t *rowptr, int32_t n, hipStream_t s, int64_t *out);

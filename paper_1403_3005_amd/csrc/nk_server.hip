@@ -429,7 +429,9 @@ nk_status nk_server_add_graph(nk_server *sv, const int32_t *rowptr, const int32_
     if (tuning_cache_active()) {
         int64_t dmax = 0;
         if ((st = graph_max_degree(g.rowptr, n, s, &dmax)) != NK_OK) return cleanup(st);
-        g.tuned = cached_tuning(n, m, dmax, &g.tuning);
+        // (requests run on the per-source kernels: an entry timed on another says nothing)
+        bool in_lds = false;
+        g.tuned = cached_tuning(n, m, dmax, &g.tuning, &in_lds) && !in_lds;
     }
     (void)hipStreamDestroy(s);
     std::lock_guard<std::mutex> lk(sv->mu);

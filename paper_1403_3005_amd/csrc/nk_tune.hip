@@ -40,10 +40,12 @@ static std::string bucket_key(int32_t n, int64_t m, int64_t maxdeg) {
 // The cache file is a flat JSON object:
 // {"key": [block, bu_ratio, bw_ratio, wg_per_cu, batch, ms, kernel_flags,
 // group], ...}, kernel_flags being the winner's tuning flag bits 3 and 4
-// (group kernel forced or forbidden); entries of six values (no kernel
+// (group kernel forced or forbidden) and kEntryInLds where the first trials
+// ran on a kernel of nk_lds.hip; entries of six values (no kernel
 // choice: the flags stay the caller's, group 0) and of four values
 // [block, bu_ratio, bw_ratio, ms] (also wg_per_cu = 0, batch = 0) are read
 // too.
+static const int32_t kEntryInLds = 256;
 static std::map<std::string, std::vector<double>> read_cache(const char *path) {
     std::map<std::string, std::vector<double>> out;
     if (!path) return out;
@@ -139,7 +141,8 @@ bool tuning_cache_active() {
     return !g_active_path.empty();
 }
 
-bool cached_tuning(int32_t n, int64_t m, int64_t max_deg, nk_tuning *out) {
+bool cached_tuning(int32_t n, int64_t m, int64_t max_deg, nk_tuning *out, bool *in_lds) {
+    *in_lds = false;
     if (t_trials) return false;
     const nk_tuning base = tuning_get();
     std::lock_guard<std::mutex> lk(g_cache_mu);
@@ -148,6 +151,7 @@ bool cached_tuning(int32_t n, int64_t m, int64_t max_deg, nk_tuning *out) {
     if (it == g_active.end()) return false;
     *out = base;
     merge_entry(it->second, out);
+    *in_lds = it->second[6] >= 0.0 && ((int32_t)it->second[6] & kEntryInLds);
     return true;
 }
 
@@ -229,9 +233,27 @@ nk_status nk_autotune(const int32_t *rowptr, const int32_t *colidx, int32_t n, i
         return true;
     };
     // stage 1: block size x the two direction thresholds, one source per task
+    // (those that the kernel looks at: with the source's state in LDS every
+    // backward level pulls, with the graph there too every forward one is
+    // top-down)
     const int blocks[] = {256, 512, 1024};
-    const float bus[] = {0.0f, 2.0f, 8.0f, 16.0f, 64.0f};
-    const float bws[] = {0.0f, 0.1f, 0.25f, 1.0f};
+    std::vector<float> bus = {0.0f, 2.0f, 8.0f, 16.0f, 64.0f}, bws = {0.0f, 0.1f, 0.25f, 1.0f};
+    bool in_lds = false;
+    {
+        nk_tuning t = saved;
+        t.batch = 1;
+        t.flags = (saved.flags & ~24) | 16;
+        TuningOverride first(&t);
+        LaunchPlan lp;
+        StatePlan sp;
+        if (plan_lds(lds_graph_bytes(n, m), n, k, &lp)) {
+            in_lds = true;
+            bus = {saved.bu_ratio};
+        } else {
+            in_lds = plan_state(n, k, &sp);
+        }
+        if (in_lds) bws = {saved.bw_ratio};
+    }
     for (int b : blocks)
         for (float bu : bus)
             for (float bw : bws) {
@@ -310,7 +332,7 @@ nk_status nk_autotune(const int32_t *rowptr, const int32_t *colidx, int32_t n, i
         auto c = read_cache(cache_path);
         c[bucket_key(n, m, dmax)] = {(double)win.block, (double)win.bu_ratio, (double)win.bw_ratio,
                                      (double)win.wg_per_cu, (double)win.batch, best_ms,
-                                     (double)(win.flags & 24), (double)win.group};
+                                     (double)((win.flags & 24) | (in_lds ? kEntryInLds : 0)), (double)win.group};
         if (!write_cache(cache_path, c)) return fail(NK_E_INVALID_ARG, "cannot write %s", cache_path);
         if (g_active_path == cache_path) g_active = c;
     }
