@@ -452,6 +452,12 @@ nk_status plan_launch(int mode, int32_t n_max, long long ntasks, int max_slots, 
         // every compute unit
         if (grid > fit) grid = fit > di.cus ? fit / di.cus * di.cus : fit;
     }
+    if ((mode == kModePair || mode == kModePairHash) && max_slots == 0) {
+        // few workgroups, the device to themselves: the form with all registers
+        const KernelRef roomy = brandes_kernel(mode, block, true);
+        NK_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, roomy.fn, block, dyn));
+        if (grid <= (long long)di.cus * occ) kr = roomy;
+    }
     plan->mode = mode;
     plan->block = block;
     plan->lds = lds;

@@ -203,6 +203,7 @@ struct KernelRef {
     void (*launch)(dim3 grid, dim3 block, size_t lds, hipStream_t s, const Params &p);
 };
 
+// (pair modes have no bitmap: true picks the form with all registers)
 KernelRef brandes_kernel(int mode, int block, bool bitmap_in_lds);
 
 // All-in-LDS betweenness kernel for graphs whose CSR and per-source state

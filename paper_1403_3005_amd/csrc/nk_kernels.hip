@@ -1538,6 +1538,14 @@ __device__ void pair_level(const Params &p, Tile<BLOCK> &sm, BiState &bs, const 
                 act[j] = e[j] != nullptr && (dz < 0 || dz == dep + 1);
                 add[j] = act[j] ? sm.val.u[kk[j]] : 0ULL;
             }
+            // (the row pointers on their way beside the adds)
+            int32_t ra[kChunk], rb1[kChunk];
+#pragma unroll
+            for (int j = 0; j < kChunk; ++j) {
+                const uint32_t v = act[j] ? (uint32_t)w[j] : 0u;
+                ra[j] = g.rp[v];
+                rb1[j] = g.rp[v + 1u];
+            }
 #pragma unroll
             for (int j = 0; j < kChunk; ++j) old[j] = act[j] ? atomicAdd(&e[j]->sig[X], add[j]) : 1ULL;
 #pragma unroll
@@ -1554,8 +1562,8 @@ __device__ void pair_level(const Params &p, Tile<BLOCK> &sm, BiState &bs, const 
                 if (fresh) {
                     e[j]->d[X] = dep + 1;
                     filter_add(filt, w[j]);
-                    a0 = g.rp[w[j]];
-                    dg = g.rp[w[j] + 1] - a0;
+                    a0 = ra[j];
+                    dg = rb1[j] - a0;
                     met = dother[j] >= 0;
                     dsum += (unsigned long long)dg;
                 }
@@ -2020,16 +2028,19 @@ __device__ void bidir_sample(const Params &p, Tile<BLOCK> &sm, BiState &bs, cons
 // Waves per SIMD asked of the compiler.  A pair sample is a chain of dependent
 // round trips, so what counts is the samples in flight: four 256-thread
 // workgroups per compute unit (all that their 38 KB of LDS allows) against
-// the two that 170 registers a lane allow (Chung-Lu 10^6, 26,500 samples:
-// kernel 3.94 -> 2.98 ms; three per compute unit 3.20 ms).  The other modes
-// come to about 128 registers, the most that four waves a SIMD may have; a few
-// more, and a compute unit holds one 512-thread workgroup instead of two.
-constexpr int min_waves(int block, int mode) {
-    return (mode == kModePair || mode == kModePairHash) && block != 256 ? 1 : 4;
+// the two that 174 registers a lane allow (Chung-Lu 10^6, 26,500 samples:
+// kernel 3.80 -> 2.88 ms).  Where the records leave room for two workgroups a
+// compute unit only, the form that keeps its registers is the faster one
+// (4 * 10^6: 6.42 -> 5.97 ms); it goes by the name of the LDS bitmap, which pair
+// modes do not have.  The other modes come to about 128 registers, the most
+// that four waves a SIMD may have; a few more, and a compute unit holds one
+// 512-thread workgroup instead of two.
+constexpr int min_waves(int block, bool roomy, int mode) {
+    return (mode == kModePair || mode == kModePairHash) && (block != 256 || roomy) ? 1 : 4;
 }
 
 template <int BLOCK, bool BMLDS, int MODE>
-__global__ __launch_bounds__(BLOCK, min_waves(BLOCK, MODE)) void k_brandes(Params p) {
+__global__ __launch_bounds__(BLOCK, min_waves(BLOCK, BMLDS, MODE)) void k_brandes(Params p) {
     extern __shared__ uint32_t lds_bm[];
     __shared__ Tile<BLOCK> sm;
     __shared__ BiState bs;
