@@ -453,10 +453,17 @@ nk_status plan_launch(int mode, int32_t n_max, long long ntasks, int max_slots, 
         if (grid > fit) grid = fit > di.cus ? fit / di.cus * di.cus : fit;
     }
     if ((mode == kModePair || mode == kModePairHash) && max_slots == 0) {
-        // few workgroups, the device to themselves: the form with all registers
+        // The form with all registers, where its two workgroups a compute unit
+        // are all there is room for, and for few samples: a workgroup costs
+        // a quarter of a microsecond of adds to the call's counters at its end
+        // (us with 512 / 1024 workgroups, 1000, 3000 and 10^4 samples: G(100,
+        // 300) 255 / 400, 379 / 498 and 815 / 751; Chung-Lu 10^6 427 / 559, 667
+        // / 752 and 1543 / 1344; R-MAT scale 15 at 10^4 599 / 649).
         const KernelRef roomy = brandes_kernel(mode, block, true);
         NK_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, roomy.fn, block, dyn));
-        if (grid <= (long long)di.cus * occ) kr = roomy;
+        const long long most = (long long)di.cus * occ;
+        if (t.wg_per_cu == 0 && ntasks <= 32LL * di.cus) grid = std::min(grid, most);
+        if (grid <= most) kr = roomy;
     }
     plan->mode = mode;
     plan->block = block;
