@@ -575,6 +575,11 @@ bool plan_state(int32_t n_max, long long ntasks, StatePlan *sp) {
     return true;
 }
 
+bool state_asks_thin(const StatePlan &sp, int32_t n, long long ntasks) {
+    const nk_tuning t = tuning_get();
+    return auto_block(n) == 256 && ntasks >= 3LL * sp.lp.grid && t.block == 0 && t.wg_per_cu == 0;
+}
+
 // Where graphs of n vertices and m arcs run with their state in LDS under the
 // tuning *t but for its block and bu_ratio, those of the caller's tuning take
 // their place: *t was timed on another kernel.
@@ -1223,7 +1228,12 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
         // per-source state fits LDS; the renaming only pays where part of
         // the path counts are outside it
         StatePlan sp;
-        const bool state = !ebc && !dir && est != kEstBisect && plan_state(n, k, &sp);
+        bool thin = false;
+        bool state = !ebc && !dir && est != kEstBisect && plan_state(n, k, &sp);
+        if (state && state_asks_thin(sp, n, k)) {
+            if ((st = thin_graph(rowptr, colidx, n, m, sources, k, h, s, &thin)) != NK_OK) return st;
+            state = !thin;
+        }
         if (!state || sp.cold)
             if ((st = prepare_graph(rowptr, colidx, n, m, dst, scr, s, &g)) != NK_OK) return st;
         // a directed run renames its in-arcs with the same permutation
@@ -1281,7 +1291,6 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
             stats_record(*h, sp.lp.grid, sp.lp.block, 1, ms);
             return st;
         }
-        bool thin = false;
         // plain and linear-scaling sweeps of undirected graphs without edge
         // scores may run one source per XCD group of workgroups
         if (!ebc && !dir && est != kEstBisect && group_wanted(n, m, k)) {
@@ -1317,7 +1326,7 @@ static nk_status bc_sources_impl(const int32_t *rowptr, const int32_t *colidx, i
                 stats_record(*h, gp.lp.grid, gp.lp.block, 6, ms);
                 return st;
             }
-            thin = (h->err & kErrNarrow) != 0;
+            thin = thin || (h->err & kErrNarrow) != 0;
             clear_error();
             NK_HIP(launch_run_begin(dst, sa.acc, sa.copies * sa.x, s));
         }
@@ -2123,15 +2132,30 @@ static nk_status batch_prepare(int32_t G, const int64_t *vtx_off, const int64_t 
     TuningOverride cached_scope(use_cached ? &cached : nullptr);
     {
         TuningOverride state_scope(use_cached ? &state_cached : nullptr);
-        // those whose per-source state fits LDS leave for its kernel
-        std::vector<int32_t> rest;
+        // those whose per-source state fits LDS leave for its kernel, but for
+        // thin ones where another is the faster
+        std::vector<int32_t> rest, ask, thin;
+        std::vector<long long> ask_tab;
+        std::vector<StatePlan> plans(large.size());
+        std::vector<char> fits(large.size());
+        for (size_t i = 0; i < large.size(); ++i) {
+            const int32_t g = large[i], ng = (int32_t)(vtx_off[g + 1] - vtx_off[g]);
+            fits[i] = plan_state(ng, ng, &plans[i]);
+            if (!fits[i] || !state_asks_thin(plans[i], ng, ng)) continue;
+            ask.push_back((int32_t)i);
+            ask_tab.insert(ask_tab.end(), {vtx_off[g] + g, ng, arc_off[g], arc_off[g + 1] - arc_off[g]});
+        }
+        if (!ask.empty()) {
+            if ((st = thin_graphs(rowptr_cat, colidx_cat, ask_tab, s, &thin)) != NK_OK) return st;
+            for (size_t i = 0; i < ask.size(); ++i)
+                if (thin[i]) fits[ask[i]] = 0;
+        }
         b->n_large = 0;
-        for (int32_t g : large) {
-            const int32_t ng = (int32_t)(vtx_off[g + 1] - vtx_off[g]);
-            StatePlan sp;
-            if (plan_state(ng, 1, &sp)) {
-                mid[sp.cold].push_back(g);
-                b->state[sp.cold].n = std::max(b->state[sp.cold].n, ng);
+        for (size_t i = 0; i < large.size(); ++i) {
+            const int32_t g = large[i], ng = (int32_t)(vtx_off[g + 1] - vtx_off[g]);
+            if (fits[i]) {
+                mid[plans[i].cold].push_back(g);
+                b->state[plans[i].cold].n = std::max(b->state[plans[i].cold].n, ng);
             } else {
                 rest.push_back(g);
                 b->n_large = std::max(b->n_large, ng);

@@ -41,12 +41,13 @@
 // so the adds into bc drain behind the following levels.  The level
 // of a vertex is a 16-bit value rather than a visited bit, so no pass marks
 // or unmarks levels.
-#include "nk_kernels.h"
+#include "nk_runtime.h"
 
 namespace nk {
 
 namespace {
 
+constexpr int kThinProbes = 8;           // searches that judge whether a graph is thin
 constexpr uint32_t kUnseen = 0xFFFFu;   // level of an unreached vertex
 constexpr int kLvlCache = 256;          // level offsets kept; deeper ones are searched
 
@@ -817,6 +818,76 @@ __global__ void k_edge_symmetrize(const int32_t *rowptr, const int32_t *colidx, 
     }
 }
 
+// Whether searches of a graph stay thin: a workgroup a search (kThinProbes a
+// graph, from vertices, or listed sources, spread over it) sets its entry of
+// `thin` to 1 if kThinProbeLevels levels hold fewer than kThinProbeFound vertices,
+// else to 0.
+// The visited set is a hash table in LDS, which the limit keeps sparse.  The
+// graph need not be valid: every index is checked.
+constexpr int32_t kThinProbeLevels = 16, kThinProbeFound = 256;
+constexpr int kThinTable = 2048;
+__device__ bool thin_search(const int32_t *rp, const int32_t *ci, int32_t n, long long m, int32_t src) {
+    __shared__ int32_t table[kThinTable], list[kThinTable];
+    __shared__ int32_t count;
+    for (int h = threadIdx.x; h < kThinTable; h += blockDim.x) table[h] = -1;
+    if (src < 0 || src >= n) return false;
+    if (threadIdx.x == 0) {
+        list[0] = src;
+        count = 1;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) table[((uint32_t)src * 2654435761u) >> 21] = src;
+    __syncthreads();
+    int32_t f0 = 0, f1 = 1;
+    for (int l = 0; l < kThinProbeLevels; ++l) {
+        for (int32_t r = f0 + wave_id(); r < f1; r += 256 / kWave) {
+            const int32_t v = list[r];
+            const long long a = rp[v], b = rp[v + 1];
+            if (a < 0 || b > m) continue;
+            for (long long e = a + lane_id(); e < b; e += kWave) {
+                if (__hip_atomic_load(&count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >= kThinProbeFound) break;
+                const int32_t u = ci[e];
+                if (u < 0 || u >= n) continue;
+                // (at most 256 vertices and one of each thread come in: a free
+                // place is found)
+                uint32_t h = ((uint32_t)u * 2654435761u) >> 21;
+                for (;; h = (h + 1) & (kThinTable - 1)) {
+                    const int32_t old = atomicCAS(&table[h], -1, u);
+                    if (old == u) break;
+                    if (old == -1) {
+                        list[atomicAdd(&count, 1)] = u;
+                        break;
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        const int32_t c = count;
+        __syncthreads();
+        if (c >= kThinProbeFound || c == f1) return false;
+        f0 = f1;
+        f1 = c;
+    }
+    return true;
+}
+
+// One graph of n vertices and m arcs, or (tab) several: four entries each, the
+// first in rowptr, the vertices, the first in colidx, the arcs.
+__global__ __launch_bounds__(256) void k_thin_probe(const int32_t *rowptr, const int32_t *colidx, int32_t n, long long m,
+                                                    const long long *tab, const int32_t *sources, long long k,
+                                                    int32_t *thin) {
+    const int32_t g = blockIdx.x, i = blockIdx.y;
+    if (tab) {
+        rowptr += tab[4 * g];
+        n = (int32_t)tab[4 * g + 1];
+        colidx += tab[4 * g + 2];
+        m = tab[4 * g + 3];
+    }
+    const long long at = (sources ? k : n) * (2 * i + 1) / (2 * kThinProbes);
+    const bool is = thin_search(rowptr, colidx, n, m, sources ? sources[at] : (int32_t)at);
+    if (threadIdx.x == 0) thin[g * kThinProbes + i] = is ? 1 : 0;
+}
+
 __global__ void k_reset_head(DevStatus *st) {
     if (threadIdx.x == 0) st->head = 0ULL;
 }
@@ -855,6 +926,44 @@ hipError_t launch_edge_symmetrize(const int32_t *rowptr, const int32_t *colidx, 
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_edge_symmetrize, dim3(1024), dim3(256), 0, s, rowptr, colidx, n, ebc, scale, st);
     return hipGetLastError();
+}
+
+nk_status thin_graph(const int32_t *rowptr, const int32_t *colidx, int32_t n, int64_t m, const int32_t *sources,
+                     long long k, DevStatus *host, hipStream_t s, bool *thin) {
+    static_assert(sizeof(host->info) == sizeof(int32_t) * kThinProbes, "an entry a probe");
+    hipLaunchKernelGGL(k_thin_probe, dim3(1, kThinProbes), dim3(256), 0, s, rowptr, colidx, n, (long long)m,
+                       (const long long *)nullptr, sources, k, host->info);
+    NK_HIP(hipGetLastError());
+    NK_HIP(hipStreamSynchronize(s));
+    int c = 0;
+    for (int32_t x : host->info) c += x;
+    *thin = c > kThinProbes / 2;
+    return NK_OK;
+}
+
+nk_status thin_graphs(const int32_t *rowptr, const int32_t *colidx, const std::vector<long long> &tab, hipStream_t s,
+                      std::vector<int32_t> *thin) {
+    Scratch scr;
+    long long *d;
+    int32_t *out;
+    nk_status st;
+    const size_t count = tab.size() / 4;
+    std::vector<int32_t> h(count * kThinProbes);
+    if ((st = scr.get((long long)tab.size(), &d)) != NK_OK) return st;
+    if ((st = scr.get((long long)h.size(), &out)) != NK_OK) return st;
+    NK_HIP(hipMemcpyAsync(d, tab.data(), sizeof(long long) * tab.size(), hipMemcpyHostToDevice, s));
+    hipLaunchKernelGGL(k_thin_probe, dim3((unsigned)count, kThinProbes), dim3(256), 0, s, rowptr, colidx, 0, 0LL, d,
+                       (const int32_t *)nullptr, 0LL, out);
+    NK_HIP(hipGetLastError());
+    NK_HIP(hipMemcpyAsync(h.data(), out, sizeof(int32_t) * h.size(), hipMemcpyDeviceToHost, s));
+    NK_HIP(hipStreamSynchronize(s));
+    thin->assign(count, 0);
+    for (size_t g = 0; g < count; ++g) {
+        int c = 0;
+        for (int i = 0; i < kThinProbes; ++i) c += h[g * kThinProbes + i];
+        (*thin)[g] = c > kThinProbes / 2;
+    }
+    return NK_OK;
 }
 
 hipError_t launch_reset_head(DevStatus *st, hipStream_t s) {

@@ -227,6 +227,22 @@ struct StatePlan {
 // for larger ones than it takes and where the tuning asks for another
 // kernel (flag bits 0, 2 and 3, or a multi-source batch).
 bool plan_state(int32_t n_max, long long ntasks, StatePlan *sp);
+// Whether so many sources of a graph of n vertices go to the one-source kernel
+// if the graph is thin: up to 2 * 10^4 vertices a compute unit runs four
+// sources there and one or two here, and a chain's level costs a barrier or two
+// on either (ms here / there: a cycle of 9,000 vertices, 512 sources 32 / 38,
+// 1024 63 / 41; 2,000 cliques of 8, 1024 sources 57 / 37; a ring lattice of
+// 12,000, 1024 21 / 16; a chain of 400 cliques of 32, 4096 40 / 36 and not thin).
+bool state_asks_thin(const StatePlan &sp, int32_t n, long long ntasks);
+// Whether most of the probed searches of a graph stay thin (nk_lds.hip), from
+// the sources (k of them, or NULL) or vertices spread over it.  Synchronises s;
+// host: the thread's pinned status, whose info it uses.
+nk_status thin_graph(const int32_t *rowptr, const int32_t *colidx, int32_t n, int64_t m, const int32_t *sources,
+                     long long k, DevStatus *host, hipStream_t s, bool *thin);
+// The same for several graphs, four entries of tab each: the first in rowptr,
+// the vertices, the first in colidx, the arcs.
+nk_status thin_graphs(const int32_t *rowptr, const int32_t *colidx, const std::vector<long long> &tab, hipStream_t s,
+                      std::vector<int32_t> *thin);
 // Scratch of the launch, and the launch.
 nk_status state_alloc(const StatePlan &sp, Params &p, Scratch &scr);
 nk_status state_enqueue(const StatePlan &sp, const Params &p, hipStream_t s);
