@@ -752,6 +752,7 @@ __device__ void bis_group(Tile<BLOCK> &sm, uint32_t *bm, const Scr &s, const GVi
             for (int32_t tb = lo; tb < hi; tb += TV) {
                 const int32_t cnt = min(TV, hi - tb);
                 if (tid < cnt * kBisK) sm.val.f[tid] = 0.0;
+                const int32_t v = tid < cnt ? s.lv[tb + tid] : 0;
                 const int32_t total = stage_list<BLOCK>(sm, s, tb, cnt);
                 __syncthreads();
                 if (tid == 0) c.arcs_bwd += (unsigned long long)total;
@@ -789,7 +790,6 @@ __device__ void bis_group(Tile<BLOCK> &sm, uint32_t *bm, const Scr &s, const GVi
                 }
                 __syncthreads();
                 if (tid < cnt) {
-                    const int32_t v = s.lv[tb + tid];
                     double *x = vec + (long long)v * kBisK;
                     const double sg = (double)s.sigma[v];
                     double add = 0.0;
@@ -835,9 +835,13 @@ __device__ void backward(const Params &p, Tile<BLOCK> &sm, uint32_t *bm, const S
         }
     }
     __syncthreads();
+    // (bisection is for vertex scores of undirected graphs: the branches that
+    // could not run cost its registers)
+    double *ebc = BIS ? nullptr : p.ebc;
+    const bool directed = BIS ? false : p.directed;
     // edge scores need the source's own arcs too: sweep down to level 0
     // (the source's dependency is not a score and is not added)
-    const int32_t lmin = p.ebc ? 0 : 1;
+    const int32_t lmin = ebc ? 0 : 1;
     for (int32_t l = Ld - 1; l >= lmin; --l) {
         const int32_t lo = s.lvl[l], hi = s.lvl[l + 1], hi1 = s.lvl[l + 2];
         // linear scaling: the pair weights d(s,v)/d(s,t) factor as l/(l+1)
@@ -849,21 +853,21 @@ __device__ void backward(const Params &p, Tile<BLOCK> &sm, uint32_t *bm, const S
         // scan whichever side of the level pair has fewer arcs (a push
         // scans in-arcs, which a directed run has only with the in-arc CSR;
         // its level degree sums count out-arcs, the proxy used there too)
-        const bool push = (!p.directed || p.trowptr) &&
+        const bool push = (!directed || p.trowptr) &&
                           (double)s.ldeg[l + 1] < (double)p.bw_ratio * (double)s.ldeg[l];
         phase_start<BLOCK>(sm);
         if (push) {
             if (tid == 0) c.bw_push++;
-            if (p.directed) {
+            if (directed) {
                 GView gin = g;
                 gin.rp = g.trp;
                 gin.ci = g.tci;
                 bw_push<BLOCK>(sm, bm, s, gin, lo, hi, hi, hi1, bcg, wfac, owt, true, p.iso, nullptr, l >= 1, c);
             } else {
-                bw_push<BLOCK>(sm, bm, s, g, lo, hi, hi, hi1, bcg, wfac, owt, false, nullptr, p.ebc, l >= 1, c);
+                bw_push<BLOCK>(sm, bm, s, g, lo, hi, hi, hi1, bcg, wfac, owt, false, nullptr, ebc, l >= 1, c);
             }
         } else {
-            bw_pull<BLOCK>(sm, bm, s, g, lo, hi, bcg, wfac, owt, p.ebc, l >= 1, c);
+            bw_pull<BLOCK>(sm, bm, s, g, lo, hi, bcg, wfac, owt, ebc, l >= 1, c);
         }
         if (push) phase_end<BLOCK>(sm, kPhPush); else phase_end<BLOCK>(sm, kPhPull);
         for (int32_t i = lo + tid; i < hi; i += BLOCK) bit_clear(bm, s.lv[i]);
