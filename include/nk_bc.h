@@ -527,7 +527,8 @@ nk_status nk_get_tuning(nk_tuning *t);
  * task (block 1024) and, where its bitmap fits LDS, the group kernel
  * (flags bit 3) with group = 2, 4 and 8 workgroups per source, those
  * compared with the fastest of the others on the sample repeated to
- * sixteen sources per compute unit, and returns the fastest in *best (HOST).  The current tuning is left unchanged.  If
+ * sixteen sources per compute unit, and returns the fastest in *best
+ * (HOST).  The current tuning is left unchanged.  If
  * cache_path is not NULL the winner is stored there under the graph's
  * shape bucket (floor log2 n, round log2 mean degree, round log2 max
  * degree / mean degree) in a flat JSON object

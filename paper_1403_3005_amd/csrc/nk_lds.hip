@@ -14,8 +14,12 @@
 //       read from global memory (it stays in L2: every workgroup reads the
 //       same one) and levels run bottom-up where that scans fewer arcs.
 //       Path counts of the vertices past `hot` (0 when all fit) live in a
-//       per-workgroup global array; in degree order those are the vertices
-//       with the fewest arcs.
+//       per-workgroup global array: a single graph runs in degree order, so
+//       those are the vertices with the fewest arcs, and its isolated ones are
+//       left out; a batch's graphs run under their own ids, where they are
+//       whatever comes last (25,000 vertices of preferential attachment, exact:
+//       40 ms with the hubs first, 54 with shuffled ids, 58 either way on the
+//       one-source kernel).
 //
 // Tasks are (graph, source) pairs, drawn from one dynamic counter, for a
 // single graph or for a batch of concatenated graphs.
