@@ -19,7 +19,7 @@
 // levels read little; a vertex stops scanning once all its missing bits are
 // found, and one that every live search has reached is skipped.  R-MAT-18
 // (8 * 10^6 arcs), 1024 sources: 0.83 ms a call, of which the two dense levels
-// are 0.24 each; 12.9 ms with one workgroup per search, which reads every arc
+// are 0.21 and 0.29; 12.9 ms with one workgroup per search, which reads every arc
 // once per source.
 //
 // A level is a launch, so graphs of many levels go to the one-workgroup-per-

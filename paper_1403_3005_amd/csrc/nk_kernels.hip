@@ -982,8 +982,9 @@ __device__ int32_t w_distances(const Params &p, Tile<BLOCK> &sm, uint32_t *bm, c
                 // the minima, then the marks, then one append a list, so that
                 // each step's atomics are in flight together (R-MAT scale 17,
                 // 256 sources: 19.6 ms to 18.7).  What is left is the heads'
-                // distances: four arcs in five read one, a line each from
-                // beyond L2 (4.6 TB/s of lines)
+                // distances: four arcs in five read one, a line each, half of
+                // them from beyond L2 (2.7 * 10^10 misses and 3.2 TB a second
+                // over the whole run, the waves waiting 76% of their cycles)
                 unsigned long long old[kChunk];
                 bool first[kChunk], queue[kChunk], far[kChunk];
 #pragma unroll
