@@ -586,7 +586,7 @@ __device__ __forceinline__ void lds_source(const Params &p, LdsShared &S, const 
 // degree order puts all of them): the first v with rp[v] = m.  Clearing,
 // listing and scanning them cost every source (6 * 10^4 vertices of which 300
 // have arcs, 1024 sources: 3.8 ms to 0.85; 2 * 10^4 of mean degree 4 and as many
-// isolated, 4096 sources: 5.0 to 2.2).
+// isolated, 4096 sources: 4.9 to 2.5).
 template <int BLOCK>
 __device__ __forceinline__ int32_t without_isolated(const int32_t *rp, int32_t n, int32_t m, int32_t *count) {
     int32_t lo = 0, step = n;
@@ -622,8 +622,14 @@ __global__ __launch_bounds__(BLOCK) void k_brandes_lds(Params p) {
     LdsCounters c = {0, 0, 0, 0, 0, 0, 0, 0};
     // (a batch's graphs are not in degree order)
     const int32_t live = CSR || p.G > 0 ? p.n : without_isolated<BLOCK>(p.rowptr, p.n, p.m, &S.nnew[0]);
-    // (the room of their levels in LDS takes path counts, less the roundings)
-    const int32_t hot = COLD ? p.lds_hot + max(0, (p.n - live) / 4 - 3) : 0;
+    // The vertices left out keep a level that is none, so that an arc into one
+    // (the graph need not be symmetric to be safe) passes for an arc to a
+    // visited vertex, as in the one-source kernel.
+    if (!CSR && live < p.n) {
+        const size_t at = (8 * (size_t)(COLD ? min(live, p.lds_hot) : live) + 15) / 16 * 16;
+        uint16_t *d = reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(lds_dyn) + at);
+        for (int32_t i = live + tid; i < p.n; i += BLOCK) d[i] = 0xFFFEu;
+    }
     for (;;) {
         const long long task = S.task;
         if (task >= p.ntasks) break;
@@ -666,14 +672,14 @@ __global__ __launch_bounds__(BLOCK) void k_brandes_lds(Params p) {
         } else {
             LdsGraph<CSR, COLD> L;
             char *q = reinterpret_cast<char *>(lds_dyn);
-            L.hot = COLD ? hot : n;
+            L.hot = COLD ? p.lds_hot : n;
             L.sig = reinterpret_cast<unsigned long long *>(q);
             q += 8 * (size_t)(COLD ? min(n, L.hot) : n);
             L.cold = COLD ? p.sigma + (long long)blockIdx.x * p.stride : nullptr;
             // (16-byte alignment of the levels)
             q += (16 - ((size_t)(q - reinterpret_cast<char *>(lds_dyn)) & 15)) & 15;
             L.d = reinterpret_cast<uint16_t *>(q);
-            q += 2 * (size_t)(((n + 7) >> 3) << 3);
+            q += 2 * (size_t)((((CSR || p.G > 0 ? n : p.n) + 7) >> 3) << 3);
             if (COLD) {
                 L.lv = reinterpret_cast<uint16_t *>(p.lv + (long long)blockIdx.x * p.stride);
             } else {
